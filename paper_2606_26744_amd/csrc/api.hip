@@ -698,6 +698,7 @@ static hdf_status draft_block_impl(const hdf_drafter* w, int n_seq, int B, const
     aa.kb = kb; aa.vtb = vtb; aa.capb = capb;
     aa.n_seq = n_seq; aa.nh = nh; aa.hd = hd; aa.B = B; aa.QB = ((B + 15) / 16) * 16;
     aa.n_chunks = n_chunks; aa.chunk_len = P.chunk_len;
+    aa.scale = float(1.0 / sqrt(double(hd)));
     aa.scale_log2 = float(1.4426950408889634 / sqrt(double(hd)));
     aa.part_o = part_o; aa.part_ml = part_ml;
     aa.fuse_epi = fuse_epi ? 1 : 0;

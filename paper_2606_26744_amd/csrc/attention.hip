@@ -12,7 +12,8 @@
 // page page_table[s][j]; its block keys sit in 64-row slot s of separate block buffers
 // of the same layout.
 //
-// bf16 kernel: grid (chunk, head, sequence x 16-query group), 8 waves.
+// Kernel (bf16; fp32 as noted at the code): grid (head, sequence x 16-query group, chunk),
+// 8 waves.
 // With one chunk (n_chunks == 1) a workgroup takes all of its sequence's context
 // tiles and the block's tile and writes the normalised output rows.  Otherwise
 // chunks 0 .. n_chunks-1 take chunk_len context keys each and chunk n_chunks the
@@ -34,6 +35,8 @@
 // sequence's new context rows into the cache, its block rows' Q into the Q buffer and K,
 // V into the block buffers, all read back only by this workgroup; that saves the
 // epilogue's own launch.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "qkv_epi.hpp"
@@ -52,15 +55,46 @@ __device__ __forceinline__ int attn_ctx_chunks(const AttnArgs& a, int T) {
   return min(a.n_chunks, (T + a.chunk_len - 1) / a.chunk_len);
 }
 
+// The softmax's exponential: scores are kept in base 2 for bf16 (one instruction, far below
+// the rounding of the operands) and in base e for fp32, as precise as expf.
+template <typename T>
+__device__ __forceinline__ float soft_exp(float x) {
+  return sizeof(T) == 2 ? fast_exp2(x) : expf(x);
+}
+
+// Eight consecutive elements a lane: one 16-byte load (bf16) or two (fp32), past the caches.
+struct F32x8 {
+  u32x4 v[2];
+  __device__ __forceinline__ float get(int e) const { return __uint_as_float(v[e >> 2][e & 3]); }
+};
+__device__ __forceinline__ F32x8 ld_nt32(const float* p) { return {ld_nt16(p), ld_nt16(p + 4)}; }
+
+// Sixteen rows x eight k a lane group against sixteen columns: the bf16 operands' product
+// as eight fp32 ones, product e taking k 8g + e of each lane group g.
+__device__ __forceinline__ f32x4_t mma_f32x8(const F32x8& a, const F32x8& b, f32x4_t c) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.get(e), b.get(e), c, 0, 0, 0);
+  return c;
+}
+
 constexpr int kAttnWaves = 8;
 constexpr int kAttnThreads = 64 * kAttnWaves;
 
 // Two waves per SIMD (one workgroup per CU): 256 VGPRs per wave at most.
 // FUSE: the workgroup first runs the projection epilogue of its (sequence, head) (AttnArgs
 // fuse_epi; only with one workgroup per (sequence, head)).
-template <int HD, bool FUSE>
+// T = float: the same tiles on v_mfma_f32_16x16x4_f32.  A bf16 operand's eight k of a lane
+// are eight fp32 products' k, so the cache layout serves both; a tile's values are loaded
+// after its scores (the keys alone fill half of the registers), and P needs no split.
+// Bound by the fp32 matrix rate (a 64-key tile of a wave is 64*HD MFMA passes against 512*HD
+// bytes).  One thread per query over all keys in turn took 1945 us a layer at 4 sequences x
+// 512 positions x 16 heads of 64; the whole two-layer step went from 4961 to 993 us.
+template <typename T, int HD, bool FUSE>
 __global__ void __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)))
-attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
+attn_kernel(AttnArgs a, T* __restrict__ out) {
+  constexpr bool F32 = sizeof(T) == 4;
+  static_assert(!(F32 && FUSE), "the fused epilogue's launch is bf16");
   constexpr int NJ = HD / 32;   // MFMA steps over the head dimension for S
   constexpr int NDT = HD / 16;  // 16-row tiles of O^T
   __shared__ float red_o[kAttnWaves][16][HD + 1];
@@ -104,10 +138,10 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
   const int wid = threadIdx.x >> 6;
   const int g = lane >> 4;       // lane group 0..3
   const int ql = lane & 15;      // query within the group / row within a sub-tile
-  const int T = a.ctx_len[s];
+  const int n_ctx = a.ctx_len[s];
   const bool direct = a.n_chunks == 1;
   const bool blk_chunk = chunk == a.n_chunks;   // the block's own workgroup
-  if (!direct && !blk_chunk && chunk >= attn_ctx_chunks(a, T)) return;  // past the context
+  if (!direct && !blk_chunk && chunk >= attn_ctx_chunks(a, n_ctx)) return;  // past the context
 
   if constexpr (FUSE) {
     // Head h of this sequence's projected rows, 16 rows a round: threads 0-255 its
@@ -128,10 +162,10 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
       if (half == 0) {
         const int r0 = c0 + it * kQkvRows;
         const int rows = max(0, min(kQkvRows, c1 - r0));
-        qkv_epi_tile<bf16_t, HD>(a.epi_ctx, rows > 0 ? r0 : 0, rows, h, et, esm[0]);
+        qkv_epi_tile<T, HD>(a.epi_ctx, rows > 0 ? r0 : 0, rows, h, et, esm[0]);
       } else {
         const int rows = max(0, min(kQkvRows, a.B - it * kQkvRows));
-        qkv_epi_tile<bf16_t, HD>(a.epi_blk, rows > 0 ? s * a.B + it * kQkvRows : 0, rows, h, et,
+        qkv_epi_tile<T, HD>(a.epi_blk, rows > 0 ? s * a.B + it * kQkvRows : 0, rows, h, et,
                                  esm[1]);
       }
     }
@@ -142,14 +176,14 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
   // Context keys [k_lo, k_hi) of the chunk in 64-row tiles (the sequence's tile t is
   // cache tile kv_offsets[s]/64 + t, or page page_table[s][t] of a paged cache); the
   // block's tile (B keys, slot s of the block buffers) follows them.
-  const int k_lo = blk_chunk ? 0 : min(T, chunk * a.chunk_len);
-  const int k_hi = blk_chunk ? 0 : min(T, k_lo + a.chunk_len);
+  const int k_lo = blk_chunk ? 0 : min(n_ctx, chunk * a.chunk_len);
+  const int k_hi = blk_chunk ? 0 : min(n_ctx, k_lo + a.chunk_len);
   const int nct = (k_hi - k_lo + kKeyTile - 1) / kKeyTile;
   const int ntiles = nct + ((direct || blk_chunk) ? 1 : 0);
-  const bf16_t* kch = static_cast<const bf16_t*>(a.kc) + int64_t(h) * a.cap * HD;
-  const bf16_t* vch = static_cast<const bf16_t*>(a.vtc) + int64_t(h) * a.cap * HD;
-  const bf16_t* kbh = static_cast<const bf16_t*>(a.kb) + int64_t(h) * a.capb * HD + lane * 8;
-  const bf16_t* vbh = static_cast<const bf16_t*>(a.vtb) + int64_t(h) * a.capb * HD + lane * 8;
+  const T* kch = static_cast<const T*>(a.kc) + int64_t(h) * a.cap * HD;
+  const T* vch = static_cast<const T*>(a.vtc) + int64_t(h) * a.cap * HD;
+  const T* kbh = static_cast<const T*>(a.kb) + int64_t(h) * a.capb * HD + lane * 8;
+  const T* vbh = static_cast<const T*>(a.vtb) + int64_t(h) * a.capb * HD + lane * 8;
   // The chunk's cache tiles go to LDS first, so the key loop has no dependent global
   // loads (each would make a wave wait for all of its outstanding tile loads).
   if (a.page_table != nullptr) {
@@ -160,24 +194,31 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
     for (int j = threadIdx.x; j < nct; j += kAttnThreads) ctile[j] = t0 + j;
   }
   __syncthreads();
-  // Tile i's first operand (plus this lane's 16 bytes) and its number of valid keys.
-  auto k_src = [&](int i) -> const bf16_t* {
+  // Tile i's first operand (plus this lane's eight elements) and its number of valid keys.
+  auto k_src = [&](int i) -> const T* {
     return i >= nct ? kbh + int64_t(s) * 64 * HD : kch + ctile[i] * 64 * HD + lane * 8;
   };
-  auto v_src = [&](int i) -> const bf16_t* {
+  auto v_src = [&](int i) -> const T* {
     return i >= nct ? vbh + int64_t(s) * 64 * HD : vch + ctile[i] * 64 * HD + lane * 8;
   };
   auto valid_of = [&](int i) { return i >= nct ? a.B : min(kKeyTile, k_hi - k_lo - i * kKeyTile); };
 
   // Q^T operand: lane holds Q[query ql][32j + 8g .. +7].
   const int q = qg * 16 + ql;
-  bf16x8_t qf[NJ];
+  typedef typename std::conditional<F32, F32x8, bf16x8_t>::type Op;   // a lane's eight values
+  Op qf[NJ];
   {
-    const bf16_t* qrow = static_cast<const bf16_t*>(a.q) + ((int64_t(s) * a.nh + h) * a.B + q) * HD;
+    const T* qrow = static_cast<const T*>(a.q) + ((int64_t(s) * a.nh + h) * a.B + q) * HD;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      u32x4 v = (q < a.B) ? ld16(qrow + 32 * j + 8 * g) : u32x4{0, 0, 0, 0};
-      qf[j] = __builtin_bit_cast(bf16x8_t, v);
+      const u32x4 none = {0, 0, 0, 0};
+      if constexpr (F32) {
+        qf[j].v[0] = (q < a.B) ? ld16(qrow + 32 * j + 8 * g) : none;
+        qf[j].v[1] = (q < a.B) ? ld16(qrow + 32 * j + 8 * g + 4) : none;
+      } else {
+        const u32x4 v = (q < a.B) ? ld16(qrow + 32 * j + 8 * g) : none;
+        qf[j] = __builtin_bit_cast(bf16x8_t, v);
+      }
     }
   }
 
@@ -193,38 +234,47 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
   // V^T[16dt + ql][32ks + 8g .. +7].  Each key and value is read once a call: the loads are
   // non-temporal (measured: 8 x 2048 positions 54 -> 49 us, the ragged step's 1533 ->
   // 1438 us).
-  bf16x8_t kf[4][NJ];
+  Op kf[4][NJ];
   u32x4 vf[2][NDT];
   auto load_k = [&](int i) {
-    const bf16_t* kt = k_src(i);
+    const T* kt = k_src(i);
 #pragma unroll
     for (int st = 0; st < 4; ++st)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        kf[st][j] = __builtin_bit_cast(bf16x8_t, ld_nt16(kt + (st * NJ + j) * 512));
+      for (int j = 0; j < NJ; ++j) {
+        if constexpr (F32)
+          kf[st][j] = ld_nt32(kt + (st * NJ + j) * 512);
+        else
+          kf[st][j] = __builtin_bit_cast(bf16x8_t, ld_nt16(kt + (st * NJ + j) * 512));
+      }
   };
   auto load_v = [&](int i) {
-    const bf16_t* vt = v_src(i);
+    const T* vt = v_src(i);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) vf[ks][dt] = ld_nt16(vt + (ks * NDT + dt) * 512);
   };
+  const float scale = F32 ? a.scale : a.scale_log2;
   for (int i = wid; i < ntiles; i += kAttnWaves) {
     load_k(i);
-    load_v(i);
+    if constexpr (!F32) load_v(i);
     const int nval = valid_of(i);
     float sv[4][4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
       f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[st][j], qf[j], acc, 0, 0, 0);
+      for (int j = 0; j < NJ; ++j) {
+        if constexpr (F32)
+          acc = mma_f32x8(kf[st][j], qf[j], acc);
+        else
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[st][j], qf[j], acc, 0, 0, 0);
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int key = 32 * (st >> 1) + 8 * g + 4 * (st & 1) + e;
-        sv[st][e] = (key < nval) ? acc[e] * a.scale_log2 : -INFINITY;
+        sv[st][e] = (key < nval) ? acc[e] * scale : -INFINITY;
       }
     }
     float tmax = -INFINITY;
@@ -235,7 +285,7 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
     tmax = fmaxf(tmax, __shfl_xor(tmax, 16, kWave));
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
     const float m_new = fmaxf(m_run, tmax);   // finite: every tile has a valid key
-    const float alpha = fast_exp2(m_run - m_new);
+    const float alpha = soft_exp<T>(m_run - m_new);
     m_run = m_new;
     float psum = 0.f;
     float pv[4][4];
@@ -243,7 +293,7 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
     for (int st = 0; st < 4; ++st)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        pv[st][e] = fast_exp2(sv[st][e] - m_new);
+        pv[st][e] = soft_exp<T>(sv[st][e] - m_new);
         psum += pv[st][e];
       }
     l_run = l_run * alpha + psum;
@@ -252,6 +302,28 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) oacc[dt][e] *= alpha;
 
+    if constexpr (F32) {
+      // V^T operands as they come, eight keys of a dim a lane; a partial tile's keys past
+      // the valid ones are zeroed (see below).
+      const T* vt = v_src(i);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        F32x8 pf;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pf.v[e >> 2][e & 3] = __float_as_uint(pv[2 * ks + (e >> 2)][e & 3]);
+        const int nvalid = nval - (32 * ks + 8 * g);
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) {
+          F32x8 vop = ld_nt32(vt + (ks * NDT + dt) * 512);
+          if (nval < kKeyTile) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vop.v[e >> 2][e & 3] = e < nvalid ? vop.v[e >> 2][e & 3] : 0u;
+          }
+          oacc[dt] = mma_f32x8(vop, pf, oacc[dt]);
+        }
+      }
+      continue;
+    }
     // Keys past the valid ones carry P = 0; zero their V too (the slot padding is never
     // written and may hold anything).  Only a segment's last tile is partial; its V
     // operands are masked in place (lane keys 32ks + 8g .. +7).
@@ -317,7 +389,7 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
     float o0 = 0.f, o1 = 0.f, l = 0.f;
 #pragma unroll
     for (int w = 0; w < kAttnWaves; ++w) {
-      const float f = (red_m[w][qq] == -INFINITY) ? 0.f : fast_exp2(red_m[w][qq] - mm);
+      const float f = (red_m[w][qq] == -INFINITY) ? 0.f : soft_exp<T>(red_m[w][qq] - mm);
       o0 += f * red_o[w][qq][dim];
       o1 += f * red_o[w][qq][dim + 1];
       l += f * red_l[w][qq];
@@ -325,9 +397,13 @@ attn_bf16_kernel(AttnArgs a, bf16_t* __restrict__ out) {
     if (direct) {
       const int qo = qg * 16 + qq;
       if (qo < a.B) {
-        const float inv = 1.f / l;
-        *reinterpret_cast<uint32_t*>(out + (int64_t(s) * a.B + qo) * (a.nh * HD) +
-                                     int64_t(h) * HD + dim) = pack_bf2(o0 * inv, o1 * inv);
+        T* dst = out + (int64_t(s) * a.B + qo) * (a.nh * HD) + int64_t(h) * HD + dim;
+        if constexpr (F32) {
+          *reinterpret_cast<float2*>(dst) = make_float2(o0 / l, o1 / l);
+        } else {
+          const float inv = 1.f / l;
+          *reinterpret_cast<uint32_t*>(dst) = pack_bf2(o0 * inv, o1 * inv);
+        }
       }
     } else {
       *reinterpret_cast<float2*>(a.part_o + (pidx + qq) * HD + dim) = make_float2(o0, o1);
@@ -372,7 +448,7 @@ attn_combine_kernel(AttnArgs a, T* __restrict__ out) {
     for (int c = 0; c < nc; ++c) mm = fmaxf(mm, cm[qq * NC + c]);
     float l = 0.f;
     for (int c = 0; c < nc; ++c) {
-      const float f = (cm[qq * NC + c] == -INFINITY) ? 0.f : fast_exp2(cm[qq * NC + c] - mm);
+      const float f = (cm[qq * NC + c] == -INFINITY) ? 0.f : soft_exp<T>(cm[qq * NC + c] - mm);
       cm[qq * NC + c] = f;
       l += f * cw[qq * NC + c];
     }
@@ -407,98 +483,42 @@ attn_combine_kernel(AttnArgs a, T* __restrict__ out) {
   }
 }
 
-// fp32 path (small correctness-size workloads): one thread per query, keys streamed
-// from the same layouts, exact expf softmax with online rescaling.
-template <int HD>
-__global__ void attn_f32_kernel(AttnArgs a, float* __restrict__ out) {
-  const int s = blockIdx.x, h = blockIdx.y;
-  const int q = threadIdx.x;
-  if (q >= a.B) return;
-  constexpr int hd = HD;
-  const int d = a.nh * hd;
-  const float* Q = static_cast<const float*>(a.q) + ((int64_t(s) * a.nh + h) * a.B + q) * hd;
-  const float scale = rsqrtf(float(hd));
-  float o[HD];
-#pragma unroll
-  for (int i = 0; i < hd; ++i) o[i] = 0.f;
-  float m = -INFINITY, l = 0.f;
-  for (int seg = 0; seg < 2; ++seg) {
-    const float* K;    // this head's keys and values
-    const float* Vt;
-    const int32_t* pt = nullptr;
-    int64_t row0 = 0;  // cache row of the segment's first key (contiguous layouts)
-    int n;
-    if (seg == 0) {
-      K = static_cast<const float*>(a.kc) + int64_t(h) * a.cap * hd;
-      Vt = static_cast<const float*>(a.vtc) + int64_t(h) * a.cap * hd;
-      if (a.page_table != nullptr)
-        pt = a.page_table + int64_t(s) * a.max_pages;
-      else
-        row0 = a.kv_offsets[s];
-      n = a.ctx_len[s];
-    } else {
-      K = static_cast<const float*>(a.kb) + int64_t(h) * a.capb * hd;
-      Vt = static_cast<const float*>(a.vtb) + int64_t(h) * a.capb * hd;
-      row0 = int64_t(s) * 64;
-      n = a.B;
-    }
-    for (int j = 0; j < n; ++j) {
-      const int64_t row = pt != nullptr ? int64_t(pt[j >> 6]) * 64 + (j & 63) : row0 + j;
-      float sc = 0.f;
-      for (int i = 0; i < hd; ++i) sc = fmaf(Q[i], K[kc_index(row, i, hd)], sc);
-      sc *= scale;
-      const float mn = fmaxf(m, sc);
-      const float al = expf(m - mn);
-      const float p = expf(sc - mn);
-      l = l * al + p;
-#pragma unroll
-      for (int i = 0; i < hd; ++i)
-        o[i] = o[i] * al + p * Vt[vc_index(row, i, hd)];
-      m = mn;
-    }
-  }
-  float* dst = out + (int64_t(s) * a.B + q) * d + int64_t(h) * hd;
-#pragma unroll
-  for (int i = 0; i < hd; ++i) dst[i] = o[i] / l;
+// One launch of the attention kernel and, with several chunks, the merge.
+template <typename T>
+static hipError_t launch_attn(const AttnArgs& a, const dim3& grid, T* out, hipStream_t s) {
+  if (a.hd == 128)
+    hipLaunchKernelGGL((attn_kernel<T, 128, false>), grid, dim3(kAttnThreads), 0, s, a, out);
+  else
+    hipLaunchKernelGGL((attn_kernel<T, 64, false>), grid, dim3(kAttnThreads), 0, s, a, out);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.n_chunks == 1) return e;
+  const size_t lds = size_t(2) * 16 * (a.n_chunks + 1) * sizeof(float);
+  hipLaunchKernelGGL(attn_combine_kernel<T>, dim3(a.n_seq * ((a.B + 15) / 16), a.nh),
+                     dim3(kCombineThreads), lds, s, a, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_attention(bool bf16, const AttnArgs& args, void* out, hipStream_t s) {
   AttnArgs a = args;
   a.n_cus = device_cu_count();
   if (a.n_seq <= 0) return hipSuccess;
-  if (!bf16) {
-    if (a.hd == 128)
-      hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(a.n_seq, a.nh), dim3(64), 0, s, a,
-                         static_cast<float*>(out));
-    else
-      hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(a.n_seq, a.nh), dim3(64), 0, s, a,
-                         static_cast<float*>(out));
-    return hipGetLastError();
-  }
   if (a.n_chunks < 1 || a.chunk_len % kKeyTile != 0 || a.chunk_len > kAttnMaxChunk)
     return hipErrorInvalidValue;
   const int nqg = (a.B + 15) / 16;
   const dim3 grid(a.nh, a.n_seq * nqg, a.n_chunks == 1 ? 1 : a.n_chunks + 1);
-  bf16_t* o = static_cast<bf16_t*>(out);
   if (a.fuse_epi) {
     // The projection epilogue runs in the attention workgroups: one per (sequence, head).
-    if (a.n_chunks != 1 || nqg != 1 || a.new_offsets == nullptr) return hipErrorInvalidValue;
+    if (!bf16 || a.n_chunks != 1 || nqg != 1 || a.new_offsets == nullptr)
+      return hipErrorInvalidValue;
+    bf16_t* o = static_cast<bf16_t*>(out);
     if (a.hd == 128)
-      hipLaunchKernelGGL((attn_bf16_kernel<128, true>), grid, dim3(kAttnThreads), 0, s, a, o);
+      hipLaunchKernelGGL((attn_kernel<bf16_t, 128, true>), grid, dim3(kAttnThreads), 0, s, a, o);
     else
-      hipLaunchKernelGGL((attn_bf16_kernel<64, true>), grid, dim3(kAttnThreads), 0, s, a, o);
+      hipLaunchKernelGGL((attn_kernel<bf16_t, 64, true>), grid, dim3(kAttnThreads), 0, s, a, o);
     return hipGetLastError();
   }
-  if (a.hd == 128)
-    hipLaunchKernelGGL((attn_bf16_kernel<128, false>), grid, dim3(kAttnThreads), 0, s, a, o);
-  else
-    hipLaunchKernelGGL((attn_bf16_kernel<64, false>), grid, dim3(kAttnThreads), 0, s, a, o);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.n_chunks == 1) return e;
-  const size_t lds = size_t(2) * 16 * (a.n_chunks + 1) * sizeof(float);
-  hipLaunchKernelGGL(attn_combine_kernel<bf16_t>, dim3(a.n_seq * nqg, a.nh), dim3(kCombineThreads),
-                     lds, s, a, o);
-  return hipGetLastError();
+  return bf16 ? launch_attn(a, grid, static_cast<bf16_t*>(out), s)
+              : launch_attn(a, grid, static_cast<float*>(out), s);
 }
 
 }  // namespace hdf

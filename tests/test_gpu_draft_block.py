@@ -296,3 +296,17 @@ def test_determinism():
     h1 = case.run().clone()
     h2 = case.run().clone()
     assert torch.equal(h1, h2)
+
+
+@pytest.mark.parametrize("hd,B,ctx,new,paged",
+                         [(128, 16, [700, 64, 1], [3, 64, 1], False),      # a partial last tile
+                          (128, 20, [1300, 65], [40, 2], True),            # chunks merged, two
+                          (64, 1, [513, 40, 128], [513, 9, 0], False),     # query groups; B = 1
+                          (64, 33, [2049], [17], True)])
+def test_fp32_attention_tiles(hd, B, ctx, new, paged):
+    """fp32 attention on the matrix cores at the edges of its tiles, chunks and query groups."""
+    wl = synth.tiny_fp32()
+    wl.d = 256
+    wl.drafter = synth.DrafterShape(d=256, n_layers=1, n_heads=256 // hd, head_dim=hd, d_ff=512,
+                                    vocab=500)
+    _compare(DraftCase(wl, ctx, new, B=B, sub=31, paged=paged, spare_pages=3 if paged else 0))
