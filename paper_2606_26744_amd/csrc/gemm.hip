@@ -30,8 +30,8 @@
 //            waves in LDS, and folded into a packed 64-bit key with one atomicMax per
 //            row and tile; the logits are stored only when asked for
 //
-// fp32 (small correctness-size workloads): a plain LDS-tiled VALU kernel reading the
-// same packed weight layout, with the same epilogues.
+// fp32: the same kernel's plain K loop on v_mfma_f32_32x32x2_f32 with 4 waves of one
+// 32-column block and 32, 64 or 128 rows (notes at the code).
 #include <initializer_list>
 
 #include "common.hpp"
@@ -39,8 +39,8 @@
 
 namespace hdf {
 
-constexpr int kGemmThreads = 256;
-constexpr int kBK = 64;        // K granularity of the bf16 kernel (K % kBK == 0)
+constexpr int kBK = 64;        // K granularity of the bf16 tiles (K % kBK == 0)
+constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last half step is zero-filled)
 constexpr int kGroupRows = 8;  // row tiles per group in the tile order of tall problems
 
 __host__ __device__ __forceinline__ int64_t packed_index(int64_t n, int64_t k, int64_t K) {
@@ -79,16 +79,24 @@ __device__ __forceinline__ int unit_swizzle(int r) { return ((r >> 1) ^ (r >> 2)
 // epilogues of the matrix-core bound shapes run on it.
 // DEEP: the K loop of the matrix-core bound partial-sum tiles (128 x 512, 4 waves of 4 x 4
 // blocks, one wave per SIMD, a STAGES-unit weight ring in registers).
-template <int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1), bool PP = false,
-          bool DEEP = false>
+// T = float: the same tiles, rings and epilogues on v_mfma_f32_32x32x2_f32.  A K step is 128
+// bytes of every activation row in either type, so the fp32 step is 32 of K; a packed
+// 32 x 16 block is 32 bytes a lane (two loads), and lane l's eight values (row l%32, k
+// 8*(l/32)..+7) are the operands of eight MFMAs, each taking k pair (e, 8 + e).
+template <typename T, int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1),
+          bool PP = false, bool DEEP = false>
 __global__ void __launch_bounds__(NW * 64)
-gemm_bf16_kernel(GemmArgs p) {
+gemm_kernel(GemmArgs p) {
+  constexpr bool F32 = sizeof(T) == 4;
+  static_assert(!F32 || !(PP || DEEP || EPI == kEpiKV), "the matrix-core bound loops are bf16");
   constexpr int THREADS = NW * 64;
   constexpr int TM = BM / 32;
   constexpr int NB = NW * TN;                     // 32-column blocks of a tile
   constexpr int BN = 32 * NB;
-  constexpr int LDA = kBK + 8;                    // padded LDS row (bf16 elements)
-  constexpr int A_CHUNKS = BM * kBK / 8;           // 16-byte chunks of an activation step
+  constexpr int BK = F32 ? kBKf32 : kBK;
+  constexpr int VEC = 16 / int(sizeof(T));        // elements of a 16-byte chunk
+  constexpr int LDA = BK + VEC;                   // padded LDS row (elements)
+  constexpr int A_CHUNKS = BM * BK / VEC;          // 16-byte chunks of an activation step
   constexpr int A_CH = (A_CHUNKS + THREADS - 1) / THREADS;
   constexpr int LDC = 33;                         // padded row of a wave's 32 columns
   static_assert(EPI == kEpiPartial || NB % 4 == 0, "argmax and K/V tiles are whole 128-column slabs");
@@ -97,12 +105,12 @@ gemm_bf16_kernel(GemmArgs p) {
   // [32 columns]), and by the ARGMAX epilogue's per-wave row maxima.
   constexpr size_t kMainLds = PP     ? size_t(4) * BM * (32 + 8) * sizeof(bf16_t)   // NBUF units
                               : DEEP ? size_t(2) * BM * 32 * sizeof(bf16_t)          // two K units
-                                     : size_t(2) * BM * LDA * sizeof(bf16_t);
+                                     : size_t(2) * BM * LDA * sizeof(T);
   constexpr size_t kEpiLds = (EPI != kEpiPartial)
       ? size_t(4) * BM * LDC * sizeof(float) + (EPI == kEpiKV ? size_t(2) * BM * sizeof(int) : 0)
       : 0;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kMainLds > kEpiLds ? kMainLds : kEpiLds];
-  typedef bf16_t ATile[BM][LDA];
+  typedef T ATile[BM][LDA];
   ATile* As = reinterpret_cast<ATile*>(smem);
 
   const int tid = threadIdx.x;
@@ -141,24 +149,24 @@ gemm_bf16_kernel(GemmArgs p) {
   }
   const int m0 = m_tile * BM, n0 = n_tile * BN;
 
-  const int nk_all = p.K / kBK;
+  const int nk_all = (p.K + BK - 1) / BK;
   const int z = blockIdx.z;
   const int kt_begin = (nk_all * z) / gridDim.z;
   const int kt_end = (nk_all * (z + 1)) / gridDim.z;
   const int nk = kt_end - kt_begin;
 
-  const bf16_t* A = static_cast<const bf16_t*>(p.A);
+  const T* A = static_cast<const T*>(p.A);
   // This wave's 32-row weight blocks: block b = n_tile*NB + wid*TN + tn is sub-block
   // b%4 of 128-row group b/4 (rows past N are zero padding of the packed layout; a
   // group past the last one is clamped to it, and the columns it computes are never
   // stored).
   const int n_groups = (p.N + 127) >> 7;
-  const bf16_t* Bw[TN];
+  const T* Bw[TN];
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
     const int blk = n_tile * NB + wid * TN + tn;
     const int grp = min(blk >> 2, n_groups - 1);
-    Bw[tn] = static_cast<const bf16_t*>(p.B) +
+    Bw[tn] = static_cast<const T*>(p.B) +
              (int64_t(grp) * (p.K >> 4) * 4 + (blk & 3)) * 512 + lane * 8;
   }
 
@@ -170,6 +178,12 @@ gemm_bf16_kernel(GemmArgs p) {
       return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, act, c, 0, 0, 0);
     else
       return __builtin_amdgcn_mfma_f32_32x32x16_bf16(act, w, c, 0, 0, 0);
+  };
+  auto mma_f32 = [](float act, float w, f32x16_t c) {
+    if constexpr (EPI == kEpiArgmax)
+      return __builtin_amdgcn_mfma_f32_32x32x2f32(w, act, c, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f32_32x32x2f32(act, w, c, 0, 0, 0);
   };
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -376,13 +390,17 @@ gemm_bf16_kernel(GemmArgs p) {
     // Activation chunk c of a K-step: row c/8, 16-byte column c%8.  Rows past M are
     // clamped (their products are never stored); loads stay unpredicated so the
     // compiler's outstanding-load counting is exact.
+    // In fp32 a last step may have only 16 of its 32 K: the chunks past K repeat the row's
+    // last one here and become zeros on their way into LDS, so that whatever finite weight
+    // they meet (a clamped block) adds nothing.
     auto load_a = [&](int kt, u32x4* dst) {
-      const int64_t k = int64_t(kt_begin + min(kt, nk - 1)) * kBK;
+      const int64_t k = int64_t(kt_begin + min(kt, nk - 1)) * BK;
 #pragma unroll
       for (int i = 0; i < A_CH; ++i) {
         const int c = min(tid + i * THREADS, A_CHUNKS - 1);   // spare threads repeat the last
         const int row = min(m0 + (c >> 3), p.M - 1);
-        dst[i] = ld16(A + int64_t(row) * p.lda + k + (c & 7) * 8);
+        const int64_t kc = k + (c & 7) * VEC;
+        dst[i] = ld16(A + int64_t(row) * p.lda + (F32 ? min(kc, int64_t(p.K - VEC)) : kc));
       }
     };
     // The ring issues STAGES steps past the last one; those are never used.  Their loads
@@ -392,20 +410,23 @@ gemm_bf16_kernel(GemmArgs p) {
     // are still issued, so the compiler's outstanding-load counting stays exact.
     auto load_b = [&](int kt, u32x4* dst) {
       const bool live = kt < nk;
-      const int64_t kb = int64_t(kt_begin + (live ? kt : 0)) * (kBK / 16);
+      const int64_t kb = int64_t(kt_begin + (live ? kt : 0)) * (BK / 16);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-          const bf16_t* src = live ? Bw[tn] + (kb + q) * 4 * 512 : A;
+          const T* w = F32 ? Bw[tn] + min(kb + (q >> 1), int64_t(p.K / 16 - 1)) * 4 * 512 + (q & 1) * VEC
+                           : Bw[tn] + (kb + q) * 4 * 512;
+          const T* src = live ? w : A;
           dst[q * TN + tn] = NT ? ld_nt16(src) : ld16(src);
         }
     };
-    auto store_a = [&](const u32x4* src, int buf) {
+    auto store_a = [&](const u32x4* src, int kt, int buf) {
 #pragma unroll
       for (int i = 0; i < A_CH; ++i) {
         const int c = min(tid + i * THREADS, A_CHUNKS - 1);
-        *reinterpret_cast<u32x4*>(&As[buf][c >> 3][(c & 7) * 8]) = src[i];
+        const bool in = !F32 || (kt_begin + kt) * BK + (c & 7) * VEC < p.K;
+        *reinterpret_cast<u32x4*>(&As[buf][c >> 3][(c & 7) * VEC]) = in ? src[i] : u32x4{0, 0, 0, 0};
       }
     };
     const int arow = lane & 31;
@@ -413,13 +434,29 @@ gemm_bf16_kernel(GemmArgs p) {
     auto compute = [&](int buf, const u32x4* bq) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
+        if constexpr (F32) {   // four of the eight values of 16-K block q/2
+          u32x4 af[TM];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const bf16x8_t af =
-              *reinterpret_cast<const bf16x8_t*>(&As[buf][arow + 32 * i][q * 16 + kof]);
+          for (int i = 0; i < TM; ++i)
+            af[i] = *reinterpret_cast<const u32x4*>(
+                &As[buf][arow + 32 * i][(q >> 1) * 16 + kof + (q & 1) * VEC]);
 #pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-            acc[i][tn] = mma(af, __builtin_bit_cast(bf16x8_t, bq[q * TN + tn]), acc[i][tn]);
+          for (int e = 0; e < VEC; ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int tn = 0; tn < TN; ++tn)
+                acc[i][tn] = mma_f32(__uint_as_float(af[i][e]), __uint_as_float(bq[q * TN + tn][e]),
+                                     acc[i][tn]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            const bf16x8_t af =
+                *reinterpret_cast<const bf16x8_t*>(&As[buf][arow + 32 * i][q * 16 + kof]);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+              acc[i][tn] = mma(af, __builtin_bit_cast(bf16x8_t, bq[q * TN + tn]), acc[i][tn]);
+          }
         }
       }
     };
@@ -435,7 +472,7 @@ gemm_bf16_kernel(GemmArgs p) {
       load_a(st, ra[st]);
       load_b(st, rb[st]);
     }
-    store_a(ra[0], 0);
+    store_a(ra[0], 0, 0);
     load_a(STAGES, ra[0]);
     __syncthreads();
     // Step t (ring slot u = t % STAGES): compute with A(t) in LDS and B(t) in rb[u];
@@ -443,7 +480,7 @@ gemm_bf16_kernel(GemmArgs p) {
     // and B(t+STAGES); barrier.
     auto step = [&](int t, int u) {
       compute(t & 1, rb[u]);
-      store_a(ra[(u + 1) % STAGES], (t + 1) & 1);
+      store_a(ra[(u + 1) % STAGES], t + 1, (t + 1) & 1);
       load_a(t + 1 + STAGES, ra[(u + 1) % STAGES]);
       load_b(t + STAGES, rb[u]);
       __syncthreads();
@@ -688,96 +725,6 @@ gemm_bf16_kernel(GemmArgs p) {
   }
 }
 
-// fp32 operands: 64x64 tiles, BK = 16, each thread owns a 4x4 block of C; the
-// weights are read through the packed index.
-template <int EPI>
-__global__ void __launch_bounds__(kGemmThreads)
-gemm_f32_kernel(GemmArgs p) {
-  constexpr int BM = 64, BN = 64, BKF = 16;
-  __shared__ float As[BKF][BM + 4];
-  __shared__ float Bs[BKF][BN + 4];
-  __shared__ float Cs[BM][BN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int mt = (p.M + BM - 1) / BM;
-  const int nt = (p.N + BN - 1) / BN;
-  const int tile = remap_tile(blockIdx.x, mt * nt);
-  const int m0 = (tile % mt) * BM, n0 = (tile / mt) * BN;
-  const int nk_all = p.K / BKF;
-  const int z = blockIdx.z;
-  const int kt_begin = (nk_all * z) / gridDim.z;
-  const int kt_end = (nk_all * (z + 1)) / gridDim.z;
-  const float* A = static_cast<const float*>(p.A);
-  const float* B = static_cast<const float*>(p.B);
-  float c[4][4] = {};
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
-    const int64_t k0 = int64_t(kt) * BKF;
-    for (int i = tid; i < BM * BKF; i += kGemmThreads) {
-      const int r = i / BKF, kk = i % BKF;
-      As[kk][r] = (m0 + r < p.M) ? A[int64_t(m0 + r) * p.lda + k0 + kk] : 0.f;
-      Bs[kk][r] = (n0 + r < p.N) ? B[packed_index(n0 + r, k0 + kk, p.K)] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BKF; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c[i][j] = fmaf(a[i], b[j], c[i][j]);
-    }
-    __syncthreads();
-  }
-  if constexpr (EPI == kEpiPartial) {
-    float* C = p.C + int64_t(z) * p.M * p.N;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-        if (row < p.M && col < p.N) C[int64_t(row) * p.N + col] = c[i][j];
-      }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) Cs[ty * 4 + i][tx * 4 + j] = c[i][j];
-    __syncthreads();
-    // Four threads per row, 16 columns each, lowest column on ties.
-    const int r = tid >> 2, part = tid & 3;
-    float best = -INFINITY;
-    int bcol = 0x7FFFFFFF;
-    if (m0 + r < p.M) {
-      for (int cc = part * 16; cc < part * 16 + 16; ++cc) {
-        const int gcol = n0 + cc;
-        if (gcol < p.N) {
-          const float v = Cs[r][cc];
-          if (p.C != nullptr) p.C[int64_t(m0 + r) * p.N + gcol] = v;
-          if (v > best) {
-            best = v;
-            bcol = gcol;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int o = 1; o < 4; o <<= 1) {
-      const float ov = __shfl_xor(best, o, kWave);
-      const int oc = __shfl_xor(bcol, o, kWave);
-      if (ov > best || (ov == best && oc < bcol)) {
-        best = ov;
-        bcol = oc;
-      }
-    }
-    if (part == 0 && m0 + r < p.M && bcol != 0x7FFFFFFF)
-      atomicMax(p.keys + m0 + r, argmax_key(best, bcol));
-  }
-}
-
 __global__ void argmax_finalize_kernel(unsigned long long* keys, int64_t M, int32_t* argmax,
                                        float* max_logit) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -816,7 +763,7 @@ static void launch_bf16_deep(const GemmArgs& a, int splits, hipStream_t s) {
   constexpr int BN = 32 * kDeepWaves * kDeepBlocks;
   const int tiles = ((a.M + 127) / 128) * ((a.N + BN - 1) / BN) +
                     ((a.M2 + 127) / 128) * ((a.N2 + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_kernel<128, kDeepWaves, kDeepRing, EPI, kDeepBlocks, false, false, true>),
+  hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, kDeepWaves, kDeepRing, EPI, kDeepBlocks, false, false, true>),
                      dim3(tiles, 1, splits), dim3(kDeepWaves * 64), 0, s, a);
 }
 
@@ -828,10 +775,10 @@ static void launch_bf16_partial(const GemmArgs& a, int splits, hipStream_t s) {
                     ((a.M2 + BM - 1) / BM) * ((a.N2 + BN - 1) / BN);
   const dim3 grid(tiles, 1, splits), block(NW * 64);
   if (BM == 64)
-    hipLaunchKernelGGL((gemm_bf16_kernel<64, NW, STAGES, kEpiPartial, TN, NT>), grid, block, 0, s,
+    hipLaunchKernelGGL((gemm_kernel<bf16_t, 64, NW, STAGES, kEpiPartial, TN, NT>), grid, block, 0, s,
                        a);
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<128, NW, STAGES, kEpiPartial, TN, NT>), grid, block, 0, s,
+    hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiPartial, TN, NT>), grid, block, 0, s,
                        a);
 }
 
@@ -844,7 +791,7 @@ template <int BM>
 static void launch_bf16_argmax_tall(const GemmArgs& a, hipStream_t s) {
   constexpr int BN = 32 * 8;
   const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(8 * 64);
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, 8, 2, kEpiArgmax, 1, true>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((gemm_kernel<bf16_t, BM, 8, 2, kEpiArgmax, 1, true>), grid, block, 0, s, a);
 }
 
 template <int NW, int TN, int STAGES>
@@ -858,14 +805,37 @@ static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
   const dim3 grid(tiles, 1, 1), block(NW * 64);
   // One row tile: every weight byte is read once, so the weights stream past the caches.
   if (BM == 64)
-    hipLaunchKernelGGL((gemm_bf16_kernel<64, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
+    hipLaunchKernelGGL((gemm_kernel<bf16_t, 64, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
                        s, a);
   else if (mt == 1)
-    hipLaunchKernelGGL((gemm_bf16_kernel<128, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
+    hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
                        s, a);
   else
-    hipLaunchKernelGGL((gemm_bf16_kernel<128, NW, STAGES, kEpiArgmax, TN, (TN == 1), (TN == 2)>),
+    hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiArgmax, TN, (TN == 1), (TN == 2)>),
                        grid, block, 0, s, a);
+}
+
+// fp32 tiles: 4 waves of one 32-column block and up to 128 rows, bound by the fp32 matrix
+// rate from about 64 rows (a 32 x 16 weight block is 2 KB against 512 matrix-core cycles per
+// 32 rows) and by the weight stream below.  Rows are rounded up to 32, 64 or 128, so at most
+// half of a tile's products are padding; one row tile streams its weights past the caches.
+// 64 rows: projections of K = 1024-4096 44 -> 12.6 us (median of five shapes), the
+// 1024 x 32000 head 249 -> 53 us against 64 x 64 tiles on the vector units.
+static int f32_rows(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+
+template <int EPI>
+static void launch_f32(const GemmArgs& a, int splits, hipStream_t s) {
+  const int BM = f32_rows(a.M);
+  const int mt = (a.M + BM - 1) / BM;
+  const dim3 grid(mt * ((a.N + 127) / 128), 1, splits), block(256);
+  if (BM == 32)
+    hipLaunchKernelGGL((gemm_kernel<float, 32, 4, 4, EPI, 1, true>), grid, block, 0, s, a);
+  else if (BM == 64)
+    hipLaunchKernelGGL((gemm_kernel<float, 64, 4, 3, EPI, 1, true>), grid, block, 0, s, a);
+  else if (mt == 1)
+    hipLaunchKernelGGL((gemm_kernel<float, 128, 4, 2, EPI, 1, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((gemm_kernel<float, 128, 4, 2, EPI, 1, false>), grid, block, 0, s, a);
 }
 
 static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPlan plan,
@@ -888,13 +858,10 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
     }
     return hipGetLastError();
   }
-  const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
   if (epi == kEpiPartial)
-    hipLaunchKernelGGL(gemm_f32_kernel<kEpiPartial>, dim3(tiles, 1, plan.splits),
-                       dim3(kGemmThreads), 0, s, a);
+    launch_f32<kEpiPartial>(a, plan.splits, s);
   else
-    hipLaunchKernelGGL(gemm_f32_kernel<kEpiArgmax>, dim3(tiles, 1, 1), dim3(kGemmThreads), 0, s,
-                       a);
+    launch_f32<kEpiArgmax>(a, 1, s);
   return hipGetLastError();
 }
 
@@ -907,14 +874,27 @@ static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int nc
 
 GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
   const int ncu = device_cu_count();
-  const int nk = K / gemm_k_align(bf16);
   if (!bf16) {
-    const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    int s = (ncu + tiles - 1) / tiles;
-    const int max_s = nk / 8 > 1 ? nk / 8 : 1;
-    s = s > max_s ? max_s : (s > 8 ? 8 : s);
-    return GemmPlan{4, s < 1 ? 1 : s};
+    // A workgroup's products take 32 cycles per 32 rows and unit of K on each SIMD (the fp32
+    // matrix rate), its CU one workgroup at a time; every split writes and the next kernel
+    // reads an fp32 partial (about 1700 B a cycle over the chip).  The split with the least
+    // sum of the two, with at least two K steps each.
+    const int BM = f32_rows(M);
+    const int tiles = ((M + BM - 1) / BM) * ((N + 127) / 128);
+    const int steps = (K + kBKf32 - 1) / kBKf32;
+    int best_s = 1;
+    double best_t = 1e30;
+    for (int sp = 1; sp <= 16 && (sp == 1 || steps / sp >= 2); ++sp) {
+      const double mma = double((int64_t(tiles) * sp + ncu - 1) / ncu) * ((steps + sp - 1) / sp) * BM * kBKf32;
+      const double t = mma + double(sp) * M * N * 8.0 / 1700.0;
+      if (t < best_t - 1e-9) {
+        best_t = t;
+        best_s = sp;
+      }
+    }
+    return GemmPlan{4, best_s};
   }
+  const int nk = K / kBK;
   // One workgroup per CU works best for these weight streams: a CU holding two
   // workgroups while others hold one doubles the kernel's critical path.  Pick the
   // tile width (4, 6 or 8 waves of 32 columns) and K split whose workgroup count fills
@@ -1035,7 +1015,7 @@ hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int 
   a.plan_pos = plan_pos; a.plan_row = plan_row; a.rope_cs = rope_cs;
   a.kc = kc; a.vtc = vtc; a.cap = cap; a.kv_d = d; a.hd = hd;
   const int tiles = ((M + 127) / 128) * ((2 * d + 511) / 512);
-  hipLaunchKernelGGL((gemm_bf16_kernel<128, 8, 2, kEpiKV, 2, false, true>), dim3(tiles), dim3(512),
+  hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, 8, 2, kEpiKV, 2, false, true>), dim3(tiles), dim3(512),
                      0, s, a);
   return hipGetLastError();
 }

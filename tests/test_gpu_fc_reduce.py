@@ -64,3 +64,11 @@ def test_empty():
     H = torch.empty((0, 4, 256), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((256, 1024), dtype=torch.bfloat16, device="cuda")
     assert hdf.fc_reduce(H, hdf.pack_weight(W)).shape == (0, 256)
+
+
+@pytest.mark.parametrize("n,m,d", [(1, 1, 16), (31, 4, 36), (33, 3, 48), (64, 1, 80), (65, 4, 132),
+                                   (129, 5, 112), (300, 4, 1024), (3, 8, 1000)])
+def test_fp32_k_steps(n, m, d):
+    """fp32 tiles with whole and half last K steps (m*d a multiple of 16 only), K below one
+    step, K splits, and row counts around 32, 64 and 128."""
+    _case(n, m, d, "f32", n + m, n % 2 == 1)

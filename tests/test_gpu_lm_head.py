@@ -172,3 +172,11 @@ def test_determinism():
     a1, m1, l1 = hdf.lm_head_argmax(hid, wp, want_logits=True)
     a2, m2, l2 = hdf.lm_head_argmax(hid, wp, want_logits=True)
     assert torch.equal(a1, a2) and torch.equal(m1, m2) and torch.equal(l1, l2)
+
+
+@pytest.mark.parametrize("M,d,V", [(1, 64, 100), (32, 320, 4100), (33, 128, 513), (64, 1024, 5000),
+                                   (65, 192, 2049), (128, 256, 1000), (130, 64, 129), (300, 512, 640)])
+def test_fp32_tiles(M, d, V):
+    """fp32 tiles at the edges of their row counts (32, 64, 128 and several) and columns."""
+    hid, w = _inputs(M, d, V, "f32", M + V + 7)
+    _check(hid, w, dtype="f32")
