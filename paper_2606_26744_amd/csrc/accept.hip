@@ -1,6 +1,7 @@
 // Greedy acceptance (Sec. 1: the target keeps the longest agreeing draft prefix;
 // Sec. 3.4: tau, the accepted length per round), optionally preceded by the LM head's
-// argmax finalisation (hdf_accept_keys).
+// argmax finalisation (hdf_accept_keys) or by the drawn tokens of the sampled verification
+// (hdf_accept_sample).
 //
 // One workgroup of 16 waves, sequences in chunks of 1024:
 //   1. one wave per sequence: its lanes compare 64 draft positions at once (ballot of
@@ -20,19 +21,29 @@ constexpr int kAcceptWaves = kAcceptThreads / kWave;
 // 0 .. M-1 into argmax (and max_logit) and clears them, then reads its drafts from the
 // argmax it has just written (draft points into it); the workgroup barrier with the fence
 // before it makes those stores visible to every wave.
+// drawn != NULL: the workgroup first completes the verified-token rows: the token of
+// sequence s at position drawn[s] is that of its first key, or of its second where the
+// first is empty (target points into the rows it writes).
 __global__ void __launch_bounds__(kAcceptThreads)
-accept_kernel(const int32_t* draft, int stride, const int32_t* __restrict__ target,
+accept_kernel(const int32_t* draft, int stride, const int32_t* target,
               int n_seq, int K, int32_t* __restrict__ acc, int32_t* __restrict__ anchor,
               int32_t* __restrict__ offs, int32_t* __restrict__ toks,
               unsigned long long* __restrict__ keys, int64_t M, int32_t* argmax,
-              float* __restrict__ max_logit) {
+              float* __restrict__ max_logit, const int32_t* __restrict__ drawn, int32_t* rows) {
   __shared__ int len[kAcceptThreads];     // n_s + 1, then the exclusive offsets
   __shared__ int nacc[kAcceptThreads];    // n_s
   __shared__ int wsum[kAcceptWaves];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wid = tid >> 6;
-  if (keys != nullptr) {
+  if (drawn != nullptr) {
+    for (int s = tid; s < n_seq; s += kAcceptThreads) {
+      const unsigned long long k = keys[2 * s] != 0ull ? keys[2 * s] : keys[2 * s + 1];
+      rows[int64_t(s) * (K + 1) + drawn[s]] = int32_t(0xFFFFFFFFu - uint32_t(k & 0xFFFFFFFFull));
+    }
+    __threadfence_block();
+    __syncthreads();
+  } else if (keys != nullptr) {
     for (int64_t i = tid; i < M; i += kAcceptThreads) {
       decode_argmax_key(keys[i], argmax + i, max_logit != nullptr ? max_logit + i : nullptr);
       keys[i] = 0ull;   // the workspace is handed back zeroed
@@ -110,7 +121,8 @@ hipError_t launch_accept(const int32_t* draft, int stride, const int32_t* target
                          int K, int32_t* acc, int32_t* anchor, int32_t* offs, int32_t* toks,
                          hipStream_t s) {
   hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(kAcceptThreads), 0, s, draft, stride, target,
-                     n_seq, K, acc, anchor, offs, toks, nullptr, int64_t(0), nullptr, nullptr);
+                     n_seq, K, acc, anchor, offs, toks, nullptr, int64_t(0), nullptr, nullptr,
+                     nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -120,7 +132,17 @@ hipError_t launch_accept_keys(unsigned long long* keys, int64_t M, int32_t* argm
                               int32_t* anchor, int32_t* offs, int32_t* toks, hipStream_t s) {
   hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(kAcceptThreads), 0, s, argmax + draft_off,
                      stride, target, n_seq, K, acc, anchor, offs, toks, keys, M, argmax,
-                     max_logit);
+                     max_logit, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_accept_drawn(const int32_t* draft, int stride, int32_t* rows,
+                               const int32_t* drawn, unsigned long long* keys, int n_seq, int K,
+                               int32_t* acc, int32_t* anchor, int32_t* offs, int32_t* toks,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(kAcceptThreads), 0, s, draft, stride, rows,
+                     n_seq, K, acc, anchor, offs, toks, keys, int64_t(0), nullptr, nullptr, drawn,
+                     rows);
   return hipGetLastError();
 }
 

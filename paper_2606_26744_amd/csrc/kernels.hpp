@@ -23,6 +23,12 @@ hipError_t launch_hc_reduce(bool bf16, int m, const void* H, const void* Wg, con
 hipError_t launch_accept(const int32_t* draft, int stride, const int32_t* target, int n_seq,
                          int K, int32_t* acc, int32_t* anchor, int32_t* offs, int32_t* toks,
                          hipStream_t s);
+// launch_accept against verified-token rows [n_seq][K+1] that still miss the token at
+// drawn[s], the low half of key 2s (of key 2s + 1 where that is empty), inverted.
+hipError_t launch_accept_drawn(const int32_t* draft, int stride, int32_t* rows,
+                               const int32_t* drawn, unsigned long long* keys, int n_seq, int K,
+                               int32_t* acc, int32_t* anchor, int32_t* offs, int32_t* toks,
+                               hipStream_t s);
 // The LM head's argmax finalisation and the acceptance in one workgroup: rows 0 .. M-1 of
 // keys -> argmax (and max_logit, may be NULL), keys cleared; then launch_accept's work
 // with draft = argmax + draft_off.

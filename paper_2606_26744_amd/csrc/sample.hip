@@ -18,23 +18,43 @@ namespace hdf {
 constexpr int kSampleThreads = 256;
 constexpr int kPurposeDraft = 0, kPurposeAccept = 1, kPurposeResample = 2;
 
+// 64 x 64 -> 128 bits from four 32 x 32 -> 64 products, on 32-bit halves: a half that every
+// lane shares (the row, the purpose and what the first rounds make of them) stays on the
+// scalar unit and so do the products of two such halves.
+struct U128 {
+  uint32_t w[4];
+};
+__device__ __forceinline__ U128 mul_64x64(uint32_t a0, uint32_t a1, uint64_t b) {
+  const uint32_t b0 = uint32_t(b), b1 = uint32_t(b >> 32);
+  const uint64_t p0 = uint64_t(a0) * b0;
+  const uint64_t p1 = uint64_t(a0) * b1 + (p0 >> 32);
+  const uint64_t p2 = uint64_t(a1) * b0 + uint32_t(p1);
+  const uint64_t p3 = uint64_t(a1) * b1 + (p1 >> 32) + (p2 >> 32);
+  return {{uint32_t(p0), uint32_t(p2), uint32_t(p3), uint32_t(p3 >> 32)}};
+}
+
 __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1) {
+  uint32_t v[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    v[2 * j] = uint32_t(c[j]);
+    v[2 * j + 1] = uint32_t(c[j] >> 32);
+  }
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r > 0) {
       k0 += 0x9E3779B97F4A7C15ull;
       k1 += 0xBB67AE8584CAA73Bull;
     }
-    const uint64_t hi0 = __umul64hi(0xD2E7470EE14C6C93ull, c[0]);
-    const uint64_t lo0 = 0xD2E7470EE14C6C93ull * c[0];
-    const uint64_t hi1 = __umul64hi(0xCA5A826395121157ull, c[2]);
-    const uint64_t lo1 = 0xCA5A826395121157ull * c[2];
-    const uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
-    c[0] = n0;
-    c[1] = lo1;
-    c[2] = n2;
-    c[3] = lo0;
+    const U128 x = mul_64x64(v[0], v[1], 0xD2E7470EE14C6C93ull);
+    const U128 y = mul_64x64(v[4], v[5], 0xCA5A826395121157ull);
+    const uint32_t n0 = y.w[2] ^ v[2] ^ uint32_t(k0), n1 = y.w[3] ^ v[3] ^ uint32_t(k0 >> 32);
+    const uint32_t n4 = x.w[2] ^ v[6] ^ uint32_t(k1), n5 = x.w[3] ^ v[7] ^ uint32_t(k1 >> 32);
+    v[0] = n0; v[1] = n1; v[2] = y.w[0]; v[3] = y.w[1];
+    v[4] = n4; v[5] = n5; v[6] = x.w[0]; v[7] = x.w[1];
   }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c[j] = uint64_t(v[2 * j]) | (uint64_t(v[2 * j + 1]) << 32);
 }
 
 // Uniforms of the eight entries 8*g .. 8*g+7 of one row.
@@ -51,7 +71,17 @@ __device__ __forceinline__ void uniforms8(uint64_t seed, uint64_t stream, uint64
 
 constexpr int kGroupsPerPass = 4;   // 8-entry groups each thread loads before computing
 
-__device__ __forceinline__ float gumbel(float u) { return -logf(-logf(u)); }
+// The draw as a race: argmax_v (s_v - log(-log u_v)) is argmax_v e^(s_v - m) / -log2(u_v)
+// for any m, so the entries compare by this ratio, whose numerator the log-sum-exp needs
+// anyway, and only a thread's winner takes a logarithm of it.  u = 1 (the top draw, rounded)
+// wins with an infinite ratio, as it does with an infinite score.
+__device__ __forceinline__ float race(float p, float u) {
+  return p * __builtin_amdgcn_rcpf(fabsf(__builtin_amdgcn_logf(u)));
+}
+// Perturbed score s_v - log(-log u_v) of a ratio with numerator e^(s_v - m).
+__device__ __forceinline__ float race_score(float ratio, float m) {
+  return m + (logf(ratio) + 0.36651292058166435f);   // - log(log 2)
+}
 
 __device__ __forceinline__ unsigned long long sample_key(float score, int v) {
   return (static_cast<unsigned long long>(f32_order_key(score)) << 32) |
@@ -64,22 +94,6 @@ struct RowState {
   float m, s, best;
   int idx;
 };
-
-__device__ __forceinline__ void lse_add(RowState& st, float x) {
-  if (x > st.m) {
-    st.s = st.s * __expf(st.m - x) + 1.f;
-    st.m = x;
-  } else {
-    st.s += __expf(x - st.m);
-  }
-}
-
-__device__ __forceinline__ void best_add(RowState& st, float score, int v) {
-  if (score > st.best || (score == st.best && v < st.idx)) {
-    st.best = score;
-    st.idx = v;
-  }
-}
 
 __device__ __forceinline__ void merge(RowState& a, const RowState& b) {
   if (b.s > 0.f) {
@@ -119,6 +133,11 @@ __device__ RowState block_merge(RowState st, RowState* sh) {
   return t;
 }
 
+// The drawing pass is bound by the vector unit's integer products (a Philox block of eight
+// uniforms is about 62 32-bit products after the shared halves are taken out), not by its
+// 16-byte loads: 128 rows x 129280, 43.6 -> 31.7 us with 32-bit halves in the generator and
+// the race in place of two logarithms an entry.  The pass without draws streams the rows
+// (14.7 us, 4.5 TB/s).
 // Pass over logits row `row`, columns [c0, c1) (c0 % 8 == 0): partial log-sum-exp of
 // logits * inv_t and, with SAMPLE, the Gumbel-max draw.  Partial j of the row goes to
 // part[row * n_parts + j].  Each thread loads kGroupsPerPass groups of eight logits
@@ -135,6 +154,7 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
   const float* z = logits + row * ld;
   const bool vec = (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
   RowState st{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
+  float ratio = 0.f;   // best ratio so far, numerators relative to st.m
   for (int g0 = c0 / 8 + threadIdx.x; 8 * g0 < c1; g0 += kSampleThreads * kGroupsPerPass) {
     float x[kGroupsPerPass][8];
 #pragma unroll
@@ -165,43 +185,67 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
       // One rescale per group: s <- s e^(m - m') + sum_k e^(x_k - m'), m' = max(m, max_k x_k).
       const float mn = fmaxf(st.m, gm);
       float add = 0.f;
+      float p[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) add += __expf(xs[k] - mn);
-      st.s = st.s * __expf(st.m - mn) + add;
+      for (int k = 0; k < 8; ++k) {
+        p[k] = __expf(xs[k] - mn);
+        add += p[k];
+      }
+      const float down = __expf(st.m - mn);
+      st.s = st.s * down + add;
       st.m = mn;
       if constexpr (SAMPLE) {
         float u[8];
         uniforms8(seed, stream, uint64_t(row), uint64_t(g), kPurposeDraft, u);
-        // The group's best perturbed score, lowest index first; groups come in increasing
+        // The group's best ratio, lowest index first (entries past the end have p = 0, the
+        // group's largest p = 1 or a running maximum above it); groups come in increasing
         // order, so a tie with the running best keeps the running (lower) index.
-        float gb = -INFINITY;
+        float gb = 0.f;
         int gk = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          const float sc = k < nv ? xs[k] - __logf(-logf(u[k])) : -INFINITY;
-          if (sc > gb) {
-            gb = sc;
-            gk = k;
-          }
+          const float r = race(p[k], u[k]);
+          const bool take = r > gb;
+          gb = take ? r : gb;
+          gk = take ? k : gk;
         }
-        if (gb > st.best) {
-          st.best = gb;
+        ratio = ratio == INFINITY ? ratio : ratio * down;
+        if (gb > ratio) {
+          ratio = gb;
           st.idx = 8 * g + gk;
         }
       }
     }
   }
+  if (st.idx != 0x7FFFFFFF) st.best = race_score(ratio, st.m);
   st = block_merge(st, sh);
   if (threadIdx.x == 0) part[row * n_parts + j] = st;
 }
 
-// Combines the partials of every row: lse[row] = m + log(s); token[row] = best index.
-__global__ void row_finish_kernel(const RowState* __restrict__ part, int64_t rows, int n_parts,
-                                  float* __restrict__ lse, int32_t* __restrict__ tokens) {
-  const int64_t row = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// A row's partials combined by one wave; every lane gets the result.
+__device__ __forceinline__ RowState row_combine(const RowState* __restrict__ part, int n_parts) {
+  RowState a{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};
+  for (int j = threadIdx.x & 63; j < n_parts; j += 64) merge(a, part[j]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    RowState b;
+    b.m = __shfl_xor(a.m, o, kWave);
+    b.s = __shfl_xor(a.s, o, kWave);
+    b.best = __shfl_xor(a.best, o, kWave);
+    b.idx = __shfl_xor(a.idx, o, kWave);
+    merge(a, b);
+  }
+  return a;
+}
+
+// lse[row] = m + log(s); token[row] = best index.  One wave per row.
+__global__ void __launch_bounds__(kSampleThreads)
+row_finish_kernel(const RowState* __restrict__ part, int64_t rows, int n_parts,
+                  float* __restrict__ lse, int32_t* __restrict__ tokens) {
+  const int64_t row = int64_t(blockIdx.x) * (kSampleThreads / 64) + (threadIdx.x >> 6);
   if (row >= rows) return;
-  RowState a = part[row * n_parts];
-  for (int j = 1; j < n_parts; ++j) merge(a, part[row * n_parts + j]);
+  const RowState a = row_combine(part + row * n_parts, n_parts);
+  if ((threadIdx.x & 63) != 0) return;
   if (lse != nullptr) lse[row] = a.m + logf(a.s);
   if (tokens != nullptr) tokens[row] = a.idx;
 }
@@ -222,13 +266,12 @@ size_t sample_parts_bytes(int64_t rows, int V) {
   return size_t(rows) * size_t(np) * sizeof(RowState);
 }
 
-hipError_t launch_row_softmax(const float* logits, int64_t rows, int V, int64_t ld, float inv_t,
-                              bool sample, uint64_t seed, uint64_t stream, int32_t* tokens,
-                              float* lse, void* part_ws, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  int np, ch;
+// The passes over the rows alone; n_parts partials a row are left in `part`.
+static hipError_t launch_row_pass(const float* logits, int64_t rows, int V, int64_t ld, float inv_t,
+                                  bool sample, uint64_t seed, uint64_t stream, RowState* part,
+                                  int& np, hipStream_t s) {
+  int ch;
   row_split(rows, V, np, ch);
-  RowState* part = static_cast<RowState*>(part_ws);
   const dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(np));
   if (sample)
     hipLaunchKernelGGL(row_pass_kernel<true>, grid, dim3(kSampleThreads), 0, s, logits, ld, V, np, ch,
@@ -236,25 +279,48 @@ hipError_t launch_row_softmax(const float* logits, int64_t rows, int V, int64_t 
   else
     hipLaunchKernelGGL(row_pass_kernel<false>, grid, dim3(kSampleThreads), 0, s, logits, ld, V, np,
                        ch, inv_t, seed, stream, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(row_finish_kernel, dim3(unsigned((rows + 255) / 256)), dim3(256), 0, s, part,
-                     rows, np, lse, tokens);
   return hipGetLastError();
 }
 
-// Decisions of one sequence per wave: lane i tests slot i (u q < p); n = first
-// rejection or K.  Writes n, the verified-token row prefix (drafts 0..n-1) and clears
-// the sequence's two draw keys.
-__global__ void __launch_bounds__(64)
+hipError_t launch_row_softmax(const float* logits, int64_t rows, int V, int64_t ld, float inv_t,
+                              bool sample, uint64_t seed, uint64_t stream, int32_t* tokens,
+                              float* lse, void* part_ws, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  int np = 0;
+  RowState* part = static_cast<RowState*>(part_ws);
+  const hipError_t e = launch_row_pass(logits, rows, V, ld, inv_t, sample, seed, stream, part, np, s);
+  if (e != hipSuccess) return e;
+  constexpr int kRows = kSampleThreads / 64;
+  hipLaunchKernelGGL(row_finish_kernel, dim3(unsigned((rows + kRows - 1) / kRows)),
+                     dim3(kSampleThreads), 0, s, part, rows, np, lse, tokens);
+  return hipGetLastError();
+}
+
+// One workgroup per sequence: its waves finish the log-sum-exps of its K + 1 target rows,
+// then the first wave decides: lane i tests slot i (u q < p); n = first rejection or K.
+// Writes n, the log-sum-exp of target row n, the verified-token row prefix (drafts 0..n-1)
+// and clears the sequence's two draw keys.
+constexpr int kDecideThreads = 1024;
+constexpr int kMaxSlots = 1025;   // K + 1 target rows
+
+__global__ void __launch_bounds__(kDecideThreads)
 accept_decide_kernel(const int32_t* __restrict__ draft, int draft_stride,
                      const float* __restrict__ draft_logits, const float* __restrict__ draft_lse,
                      int64_t ld, const float* __restrict__ target_logits,
-                     const float* __restrict__ target_lse, int K, int V, float inv_t,
+                     const RowState* __restrict__ part, int n_parts, int K, int V, float inv_t,
                      uint64_t seed, uint64_t stream, int32_t* __restrict__ n_out,
-                     int32_t* __restrict__ tgt, unsigned long long* __restrict__ keys) {
+                     float* __restrict__ lse_out, int32_t* __restrict__ tgt,
+                     unsigned long long* __restrict__ keys) {
+  __shared__ float lse[kMaxSlots];
   const int s = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int64_t t0 = int64_t(s) * (K + 1);
+  for (int i = wid; i <= K; i += int(blockDim.x >> 6)) {
+    const RowState a = row_combine(part + (t0 + i) * n_parts, n_parts);
+    if (lane == 0) lse[i] = a.m + logf(a.s);
+  }
+  __syncthreads();
+  if (wid != 0) return;
   int n = K;
   for (int c0 = 0; c0 < K; c0 += 64) {
     const int i = c0 + lane;
@@ -263,8 +329,7 @@ accept_decide_kernel(const int32_t* __restrict__ draft, int draft_stride,
       const int64_t dr = int64_t(s) * draft_stride + i;
       const int x = draft[dr];
       const float q = __expf(draft_logits[dr * ld + x] * inv_t - draft_lse[dr]);
-      const int64_t tr = int64_t(s) * (K + 1) + i;
-      const float p = __expf(target_logits[tr * V + x] * inv_t - target_lse[tr]);
+      const float p = __expf(target_logits[(t0 + i) * V + x] * inv_t - lse[i]);
       float u[8];
       uniforms8(seed, stream, uint64_t(s), uint64_t(i >> 3), kPurposeAccept, u);
       reject = !(u[i & 7] * q < p);
@@ -275,73 +340,91 @@ accept_decide_kernel(const int32_t* __restrict__ draft, int draft_stride,
       break;
     }
   }
-  for (int i = lane; i <= K; i += 64) {
-    tgt[int64_t(s) * (K + 1) + i] = i < n ? draft[int64_t(s) * draft_stride + i] : -1;
-  }
+  for (int i = lane; i <= K; i += 64) tgt[t0 + i] = i < n ? draft[int64_t(s) * draft_stride + i] : -1;
   if (lane == 0) {
     n_out[s] = n;
+    lse_out[s] = lse[n];
     keys[2 * s] = 0ull;
     keys[2 * s + 1] = 0ull;
   }
 }
 
 // The draw after the decisions, split over the vocabulary: workgroup (s, j) scans
-// columns [j*chunk, ...) of row n of sequence s.  Key 0: max(0, p_n - q_n) after a
-// rejection, log p_K after K acceptances; key 1: log p_n (used only if the residual
-// has no positive entry).
+// columns [j*chunk, ...) of row n of sequence s.  Key 0: the race of max(0, p_n - q_n) after
+// a rejection, of p_K after K acceptances; key 1: of p_n (used only if the residual has no
+// positive entry).  The numerators are probabilities, so the ratios of all workgroups share
+// one scale and are the keys' order as they are.  A few thousand columns a sequence and
+// workgroup: the launch is one chain of loads, generator rounds and the key reduction (8
+// sequences x 129280: 17.2 -> 7.7 us with 16-byte loads ahead of the generator and one key
+// reduction in place of two merges of log-sum-exp states).
 __global__ void __launch_bounds__(kSampleThreads)
 accept_draw_kernel(const float* __restrict__ draft_logits, const float* __restrict__ draft_lse,
                    int64_t ld, int draft_stride, const float* __restrict__ target_logits,
                    const float* __restrict__ target_lse, int K, int V, int chunk, float inv_t,
                    uint64_t seed, uint64_t stream, const int32_t* __restrict__ n_in,
                    unsigned long long* __restrict__ keys) {
-  __shared__ RowState sh[kSampleThreads / 64];
   const int s = blockIdx.x, j = blockIdx.y;
   const int n = n_in[s];
-  const int64_t tr = int64_t(s) * (K + 1) + n;
-  const float* zt = target_logits + tr * V;
-  const float lt = target_lse[tr];
+  const float* zt = target_logits + (int64_t(s) * (K + 1) + n) * V;
+  const float lt = target_lse[s];
   const bool resid = n < K;
   const int64_t dr = int64_t(s) * draft_stride + (resid ? n : 0);
-  const float* zd = draft_logits + dr * ld;
-  const float ld_ = resid ? draft_lse[dr] : 0.f;
+  const float* zd = resid ? draft_logits + dr * ld : zt;   // not read without a rejection
+  const float ldr = resid ? draft_lse[dr] : 0.f;
+  const bool vec = ((reinterpret_cast<uintptr_t>(zt) | reinterpret_cast<uintptr_t>(zd)) & 15u) == 0;
   const int c0 = j * chunk, c1 = min(V, c0 + chunk);
-  RowState a{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};   // residual / bonus
-  RowState b{-INFINITY, 0.f, -INFINITY, 0x7FFFFFFF};   // log p_n fallback
+  unsigned long long ka = 0ull, kb = 0ull;
   for (int g = c0 / 8 + threadIdx.x; 8 * g < c1; g += kSampleThreads) {
+    const int v0 = 8 * g, nv = min(8, c1 - v0);
+    float t[8], d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (vec && nv == 8) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 a = *reinterpret_cast<const float4*>(zt + v0 + 4 * h);
+        t[4 * h] = a.x; t[4 * h + 1] = a.y; t[4 * h + 2] = a.z; t[4 * h + 3] = a.w;
+        if (resid) {
+          const float4 b = *reinterpret_cast<const float4*>(zd + v0 + 4 * h);
+          d[4 * h] = b.x; d[4 * h + 1] = b.y; d[4 * h + 2] = b.z; d[4 * h + 3] = b.w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        t[k] = k < nv ? zt[v0 + k] : 0.f;
+        if (resid && k < nv) d[k] = zd[v0 + k];
+      }
+    }
     float u[8];
     uniforms8(seed, stream, uint64_t(s), uint64_t(g), kPurposeResample, u);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const int v = 8 * g + k;
-      if (v < c1) {
-        const float gm = gumbel(u[k]);
-        const float lp = zt[v] * inv_t - lt;
-        if (resid) {
-          const float w = __expf(lp) - __expf(zd[v] * inv_t - ld_);
-          if (w > 0.f) best_add(a, logf(w) + gm, v);
-          best_add(b, lp + gm, v);
-        } else {
-          best_add(a, lp + gm, v);
-        }
+      if (k < nv) {
+        const float p = __expf(t[k] * inv_t - lt);
+        const float w = resid ? p - __expf(d[k] * inv_t - ldr) : p;
+        const unsigned long long key = sample_key(race(w, u[k]), v0 + k);
+        if (w > 0.f && key > ka) ka = key;
+        const unsigned long long fall = sample_key(race(p, u[k]), v0 + k);
+        if (resid && p > 0.f && fall > kb) kb = fall;
       }
     }
   }
-  a = block_merge(a, sh);
-  b = block_merge(b, sh);
-  if (threadIdx.x == 0) {
-    if (a.idx != 0x7FFFFFFF) atomicMax(keys + 2 * s, sample_key(a.best, a.idx));
-    if (b.idx != 0x7FFFFFFF) atomicMax(keys + 2 * s + 1, sample_key(b.best, b.idx));
+  __shared__ unsigned long long sh[2][kSampleThreads / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long xa = __shfl_xor(ka, o, kWave), xb = __shfl_xor(kb, o, kWave);
+    ka = xa > ka ? xa : ka;
+    kb = xb > kb ? xb : kb;
   }
-}
-
-__global__ void accept_finish_kernel(int n_seq, int K, const int32_t* __restrict__ n_in,
-                                     const unsigned long long* __restrict__ keys,
-                                     int32_t* __restrict__ tgt) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n_seq) return;
-  const unsigned long long k = keys[2 * s] != 0ull ? keys[2 * s] : keys[2 * s + 1];
-  tgt[int64_t(s) * (K + 1) + n_in[s]] = int32_t(0xFFFFFFFFu - uint32_t(k & 0xFFFFFFFFull));
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = ka;
+    sh[1][threadIdx.x >> 6] = kb;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    unsigned long long k = 0ull;
+    for (int w = 0; w < kSampleThreads / 64; ++w) k = sh[threadIdx.x][w] > k ? sh[threadIdx.x][w] : k;
+    if (k != 0ull) atomicMax(keys + 2 * s + threadIdx.x, k);
+  }
 }
 
 size_t accept_sample_ws_bytes(int n_seq, int K, int V) {
@@ -367,12 +450,15 @@ hipError_t launch_accept_sample(const int32_t* draft, int draft_stride, const fl
   p += al(size_t(n_seq) * 16);
   int32_t* tgt = reinterpret_cast<int32_t*>(p);
   p += al(size_t(rows) * 4);
-  hipError_t e = launch_row_softmax(target_logits, rows, V, V, inv_t, false, 0, 0, nullptr, tlse,
-                                    p, s);
+  RowState* part = reinterpret_cast<RowState*>(p);
+  int tp = 0;
+  hipError_t e = launch_row_pass(target_logits, rows, V, V, inv_t, false, 0, 0, part, tp, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_decide_kernel, dim3(n_seq), dim3(64), 0, s, draft, draft_stride,
-                     draft_logits, draft_lse, ld, target_logits, tlse, K, V, inv_t, seed, stream,
-                     n_buf, tgt, keys);
+  // A wave per target row, up to sixteen.
+  const int decide = 64 * (K + 1 < kDecideThreads / 64 ? K + 1 : kDecideThreads / 64);
+  hipLaunchKernelGGL(accept_decide_kernel, dim3(n_seq), dim3(decide), 0, s, draft, draft_stride,
+                     draft_logits, draft_lse, ld, target_logits, part, tp, K, V, inv_t, seed, stream,
+                     n_buf, tlse, tgt, keys);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   int np, ch;
@@ -382,14 +468,11 @@ hipError_t launch_accept_sample(const int32_t* draft, int draft_stride, const fl
                      n_buf, keys);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_finish_kernel, dim3((n_seq + 255) / 256), dim3(256), 0, s, n_seq, K,
-                     n_buf, keys, tgt);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // The verified tokens of sequence s now read drafts 0..n-1 then the draw, which differs
+  // The verified tokens of sequence s then read drafts 0..n-1 and the draw, which differs
   // from draft n (a rejected draft has p < q, so its residual weight is 0): greedy
   // acceptance against this row yields n, the draw as next anchor and the commits.
-  return launch_accept(draft, draft_stride, tgt, n_seq, K, acc, anchor, offs, toks, s);
+  return launch_accept_drawn(draft, draft_stride, tgt, n_buf, keys, n_seq, K, acc, anchor, offs,
+                             toks, s);
 }
 
 }  // namespace hdf

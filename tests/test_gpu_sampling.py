@@ -113,3 +113,28 @@ def test_accept_sample_rejects_a_draft_outside_the_target():
 
 def test_accept_sample_without_drafts_draws_the_bonus():
     _accept_case(16, 0, 700, 1.0, seed=34)
+
+
+@pytest.mark.parametrize("R,V,T", [(1, 2, 1.0), (3, 7, 1.0), (2, 8, 0.5), (1, 2049, 1.0), (5, 140003, 1.0),
+                                   (2, 151936, 0.9)])
+def test_sample_tokens_edges(R, V, T):
+    """Vocabularies of less than a group of eight, one column past a part, more parts than a
+    wave has lanes (above 131072 columns), rows that are not 16-byte aligned."""
+    _check_sample(_logits(R, V, R + V), T, seed=5, stream=1)
+
+
+def test_sample_tokens_far_below_the_maximum():
+    """Rows whose first columns lie far below the rest, and masked columns (the type's lowest
+    value): a running best must not survive a maximum it is no match for."""
+    lg = _logits(6, 40000, 3)
+    lg[:, :20000] -= 300.0
+    lg[1:, ::3] = torch.finfo(torch.float32).min
+    tok, _ = _check_sample(lg, 1.0, seed=8, stream=2)
+    assert (tok.cpu().numpy() >= 20000).all()
+
+
+@pytest.mark.parametrize("n_seq,K,V", [(1, 1, 9), (3, 2, 135001), (2, 17, 4097), (2, 70, 301)])
+def test_accept_sample_edges(n_seq, K, V):
+    """More target rows than the deciding workgroup has waves, more than 64 slots, unaligned
+    rows, and more row parts than lanes."""
+    _accept_case(n_seq, K, V, 1.0, seed=40 + K, noise=0.2)
