@@ -183,15 +183,17 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
         gm = fmaxf(gm, xs[k]);
       }
       // One rescale per group: s <- s e^(m - m') + sum_k e^(x_k - m'), m' = max(m, max_k x_k).
+      // While every entry was -inf (masked columns), the exponents refer to 0.
       const float mn = fmaxf(st.m, gm);
+      const float ref = mn == -INFINITY ? 0.f : mn;
       float add = 0.f;
       float p[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        p[k] = __expf(xs[k] - mn);
+        p[k] = __expf(xs[k] - ref);
         add += p[k];
       }
-      const float down = __expf(st.m - mn);
+      const float down = __expf(st.m - ref);
       st.s = st.s * down + add;
       st.m = mn;
       if constexpr (SAMPLE) {

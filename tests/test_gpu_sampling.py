@@ -138,3 +138,16 @@ def test_accept_sample_edges(n_seq, K, V):
     """More target rows than the deciding workgroup has waves, more than 64 slots, unaligned
     rows, and more row parts than lanes."""
     _accept_case(n_seq, K, V, 1.0, seed=40 + K, noise=0.2)
+
+
+def test_sample_tokens_masked_columns():
+    """Columns masked with -inf, whole leading groups of a thread among them: draws and
+    log-sum-exps are those of the other columns."""
+    lg = _logits(4, 30000, 17)
+    lg[:, :25000] = float("-inf")
+    tok, lse = hdf.sample_tokens(lg, seed=8, stream_id=2)
+    torch.cuda.synchronize()
+    r_tok, r_lse, margin = ref_sample(lg.cpu().numpy(), 1.0, 8, 2)
+    ok = margin >= SMARGIN
+    assert np.array_equal(tok.cpu().numpy()[ok], r_tok[ok])
+    np.testing.assert_allclose(lse.cpu().numpy(), r_lse, rtol=1e-5, atol=1e-5)
