@@ -3,8 +3,9 @@
 // path-mean target state at position a+k-1 and the draft logits z of slot k, the
 // cross entropy of the draft logits against the ground truth, and
 //     L_KL = T^2 / P * mean_blocks sum_k KL,   L = L_CE + alpha * L_KL.
-// The teacher's projection is the LM-head GEMM of gemm.hip (logits kept); the KL of a
-// row pair is one split pass over the vocabulary with online log-sum-exps.
+// Four launches: the teacher states, their projection (the LM-head GEMM of gemm.hip with
+// its logits kept), one split pass over the vocabulary of every row pair and every
+// cross-entropy row with online log-sum-exps, and the finish.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -21,31 +22,85 @@ __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return f2bf(x); }
 template <>
 __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 
-// Teacher state: mean over the m paths, RMSNorm, * gamma, rounded to T.
+// Eight consecutive elements as floats.
 template <typename T>
-__global__ void __launch_bounds__(kKlThreads)
-pool_norm_kernel(const T* __restrict__ H, int m, int d, const float* __restrict__ gamma, float eps,
-                 T* __restrict__ out) {
-  __shared__ float sh[kKlThreads / 64];
-  __shared__ float row[8192];
+__device__ __forceinline__ void load8f(const T* p, bool vec, float v[8]) {
+  if (vec) {
+#pragma unroll
+    for (int h = 0; h < 8 * int(sizeof(T)) / 16; ++h) {
+      const u32x4 x = ld16(p + h * (16 / int(sizeof(T))));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2) {
+          v[2 * e] = lo_bf(x[e]);
+          v[2 * e + 1] = hi_bf(x[e]);
+        } else {
+          v[4 * h + e] = __uint_as_float(x[e]);
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = to_f32(p[e]);
+  }
+}
+
+// Teacher state: mean over the m paths, RMSNorm, * gamma, rounded to T.  One workgroup per
+// row and eight columns a thread and group (d % 64 == 0, d <= 8192), every path's loads of
+// a row in flight together (16 rows x 4 x 4096: 23 -> 6 us against one column a thread and
+// load).  vec: H is 16-byte aligned (the state always is).
+constexpr int kPoolThreads = 512;
+
+template <typename T>
+__global__ void __launch_bounds__(kPoolThreads)
+pool_norm_kernel(const T* __restrict__ H, int m, int d, bool vec, const float* __restrict__ gamma,
+                 float eps, T* __restrict__ out) {
+  constexpr int G = 8192 / (8 * kPoolThreads);
+  __shared__ float sh[kPoolThreads / 64];
   const int64_t r = blockIdx.x;
   const T* h = H + r * int64_t(m) * d;
+  float x[G][8];
   float ss = 0.f;
-  for (int c = threadIdx.x; c < d; c += kKlThreads) {
-    float acc = 0.f;
-    for (int j = 0; j < m; ++j) acc += to_f32(h[int64_t(j) * d + c]);
-    const float x = acc / float(m);
-    row[c] = x;
-    ss = fmaf(x, x, ss);
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int c = (g * kPoolThreads + threadIdx.x) * 8;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[g][e] = 0.f;
+    if (c < d) {
+#pragma unroll 4
+      for (int j = 0; j < m; ++j) {
+        float v[8];
+        load8f(h + int64_t(j) * d + c, vec, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[g][e] += v[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        x[g][e] /= float(m);
+        ss = fmaf(x[g][e], x[g][e], ss);
+      }
+    }
   }
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
   __syncthreads();
   float tot = 0.f;
-  for (int w = 0; w < kKlThreads / 64; ++w) tot += sh[w];
+  for (int w = 0; w < kPoolThreads / 64; ++w) tot += sh[w];
   const float rs = rsqrtf(tot / float(d) + eps);
-  for (int c = threadIdx.x; c < d; c += kKlThreads)
-    out[r * d + c] = from_f32<T>(row[c] * rs * (gamma ? gamma[c] : 1.f));
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int c = (g * kPoolThreads + threadIdx.x) * 8;
+    if (c < d) {
+      T o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = from_f32<T>(x[g][e] * rs * (gamma ? gamma[c + e] : 1.f));
+      u32x4* dst = reinterpret_cast<u32x4*>(out + r * d + c);
+      u32x4 q[sizeof(o) / 16];
+      __builtin_memcpy(q, o, sizeof(o));
+#pragma unroll
+      for (int e = 0; e < int(sizeof(o) / 16); ++e) dst[e] = q[e];
+    }
+  }
 }
 
 // Online state of one part of a (teacher, student) row pair at temperature T:
@@ -78,22 +133,100 @@ __device__ __forceinline__ void kl_merge(KlState& x, const KlState& y) {
   }
 }
 
-// Row pair i = s*P + (k-1): teacher row i of tl [n*P][V]; student row s*B + k of zl (ld).
+// A part of a cross-entropy row: log-sum-exp state (m, s) of the draft logits.
+struct LseState {
+  float m, s;
+};
+__device__ __forceinline__ void lse_merge(LseState& x, const LseState& y) {
+  if (y.s > 0.f) {
+    if (x.s == 0.f) {
+      x = y;
+    } else if (y.m > x.m) {
+      x.s = x.s * __expf(x.m - y.m) + y.s; x.m = y.m;
+    } else {
+      x.s += y.s * __expf(y.m - x.m);
+    }
+  }
+}
+
+// Columns v0 .. v0+7 of a row scaled by f; columns from end on are -inf.
+__device__ __forceinline__ void load_cols(const float* __restrict__ row, int v0, int end, bool vec,
+                                          float f, float x[8]) {
+  if (vec && v0 + 8 <= end) {
+    load8f(row + v0, true, x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= f;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = v0 + e < end ? row[v0 + e] * f : -INFINITY;
+  }
+}
+
+// Log-sum-exp state of eight more values; w[e] = e^(x_e - m).  Returns what the state's
+// earlier sums were scaled by.  While every value was -inf (masked columns), the exponents
+// refer to 0, so that the sums stay 0.
+__device__ __forceinline__ float lse_add8(float& m, float& s, const float x[8], float w[8]) {
+  float mn = m;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) mn = fmaxf(mn, x[e]);
+  const float ref = mn == -INFINITY ? 0.f : mn;
+  float add = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    w[e] = __expf(x[e] - ref);
+    add += w[e];
+  }
+  const float down = __expf(m - ref);
+  s = s * down + add;
+  m = mn;
+  return down;
+}
+
+// One launch over both kinds of rows (chunks of whole groups of eight columns): the first
+// R * kl_parts workgroups take the parts of row pair i = s*P + (k-1) (teacher row i of
+// tl [n*P][V]; student row s*B + k of zl), the others those of the cross-entropy rows
+// s*B + k, k = 1..B-1.  Bound by the streams of the logits (8 x 15 rows x 129280 and 16
+// pairs: 63 + 17 MB in 16 us; two launches, one of them a column a thread and load, 23 us).
 __global__ void __launch_bounds__(kKlThreads)
 kl_pass_kernel(const float* __restrict__ tl, const float* __restrict__ zl, int64_t ld, int B, int P,
-               int V, int chunk, int n_parts, float inv_t, KlState* __restrict__ part) {
+               int V, int64_t pair_wgs, int kl_parts, int kl_chunk, int ce_parts, int ce_chunk,
+               float inv_t, KlState* __restrict__ kl_part, LseState* __restrict__ ce_part) {
   __shared__ KlState sh[kKlThreads / 64];
-  const int64_t i = blockIdx.x;
-  const int j = blockIdx.y;
-  const int64_t s = i / P, k = i - s * P + 1;
-  const float* t = tl + i * int64_t(V);
+  const bool pair = int64_t(blockIdx.x) < pair_wgs;
+  const int64_t b = pair ? blockIdx.x : blockIdx.x - pair_wgs;
+  const int parts = pair ? kl_parts : ce_parts, chunk = pair ? kl_chunk : ce_chunk;
+  const int64_t i = b / parts;
+  const int j = int(b - i * parts);
+  const int per = pair ? P : B - 1;
+  const int64_t s = i / per, k = i - s * per + 1;
   const float* z = zl + (s * B + k) * ld;
+  const bool vz = (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
   const int c0 = j * chunk, c1 = min(V, c0 + chunk);
   KlState st{-INFINITY, 0.f, 0.f, -INFINITY, 0.f};
-  for (int v = c0 + threadIdx.x; v < c1; v += kKlThreads) {
-    const float tt = t[v] * inv_t, zz = z[v] * inv_t;
-    KlState one{tt, 1.f, tt - zz, zz, 1.f};
-    kl_merge(st, one);
+  if (pair) {
+    const float* t = tl + i * int64_t(V);
+    const bool vt = (reinterpret_cast<uintptr_t>(t) & 15u) == 0;
+    for (int v = c0 + 8 * int(threadIdx.x); v < c1; v += 8 * kKlThreads) {
+      float tt[8], zz[8], wt[8], wz[8];
+      load_cols(t, v, c1, vt, inv_t, tt);
+      load_cols(z, v, c1, vz, inv_t, zz);
+      const float down = lse_add8(st.mt, st.st, tt, wt);
+      float a = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a = wt[e] > 0.f ? fmaf(wt[e], tt[e] - zz[e], a) : a;
+      st.a = st.a * down + a;
+      lse_add8(st.mz, st.sz, zz, wz);
+    }
+  } else {
+    constexpr int Q = 4;   // groups whose loads are in flight together
+    for (int v = c0 + 8 * int(threadIdx.x); v < c1; v += 8 * kKlThreads * Q) {
+      float zz[Q][8], wz[8];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) load_cols(z, v + 8 * kKlThreads * q, c1, vz, 1.f, zz[q]);
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (v + 8 * kKlThreads * q < c1) lse_add8(st.mz, st.sz, zz[q], wz);
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -106,45 +239,80 @@ kl_pass_kernel(const float* __restrict__ tl, const float* __restrict__ zl, int64
   if (threadIdx.x == 0) {
     KlState x = sh[0];
     for (int w = 1; w < kKlThreads / 64; ++w) kl_merge(x, sh[w]);
-    part[i * n_parts + j] = x;
+    if (pair)
+      kl_part[b] = x;
+    else
+      ce_part[b] = LseState{x.mz, x.sz};
   }
 }
 
 // kl[i] = a/st - (mt + log st) + (mz + log sz); ce from the student log-sum-exps; losses.
-__global__ void __launch_bounds__(kKlThreads)
-kl_finish_kernel(const KlState* __restrict__ part, int n_parts, int n_seq, int P, int B,
-                 const float* __restrict__ zl, int64_t ld, const float* __restrict__ zlse,
-                 const int32_t* __restrict__ labels, float T, float alpha,
-                 float* __restrict__ kl, float* __restrict__ ce, float* __restrict__ loss) {
-  __shared__ float sh[2][kKlThreads / 64];
+// One workgroup.  Row pairs of more than eight parts take a wave each (a part a lane; one
+// thread walking 64 parts took 33 us), all other rows a thread.
+constexpr int kFinishThreads = 1024;
+
+__device__ __forceinline__ float kl_value(const KlState& x) {
+  return x.a / x.st - (x.mt + logf(x.st)) + (x.mz + logf(x.sz));
+}
+
+__global__ void __launch_bounds__(kFinishThreads)
+kl_finish_kernel(const KlState* __restrict__ kl_part, int kl_parts,
+                 const LseState* __restrict__ ce_part, int ce_parts, int n_seq, int P, int B,
+                 const float* __restrict__ zl, int64_t ld, const int32_t* __restrict__ labels,
+                 float T, float alpha, float* __restrict__ kl, float* __restrict__ ce,
+                 float* __restrict__ loss) {
+  constexpr int W = kFinishThreads / 64;
+  __shared__ float sh[2][W];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   float skl = 0.f, sce = 0.f;
-  for (int i = threadIdx.x; i < n_seq * P; i += kKlThreads) {
-    KlState x = part[int64_t(i) * n_parts];
-    for (int j = 1; j < n_parts; ++j) kl_merge(x, part[int64_t(i) * n_parts + j]);
-    const float v = x.a / x.st - (x.mt + logf(x.st)) + (x.mz + logf(x.sz));
-    kl[i] = v;
-    skl += v;
+  if (kl_parts > 8) {
+    for (int i = wid; i < n_seq * P; i += W) {
+      KlState x{-INFINITY, 0.f, 0.f, -INFINITY, 0.f};
+      for (int j = lane; j < kl_parts; j += 64) kl_merge(x, kl_part[int64_t(i) * kl_parts + j]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        KlState y{__shfl_xor(x.mt, o, kWave), __shfl_xor(x.st, o, kWave), __shfl_xor(x.a, o, kWave),
+                  __shfl_xor(x.mz, o, kWave), __shfl_xor(x.sz, o, kWave)};
+        kl_merge(x, y);
+      }
+      if (lane == 0) {
+        const float v = kl_value(x);
+        kl[i] = v;
+        skl += v;
+      }
+    }
+  } else {
+    for (int i = threadIdx.x; i < n_seq * P; i += kFinishThreads) {
+      KlState x = kl_part[int64_t(i) * kl_parts];
+      for (int j = 1; j < kl_parts; ++j) kl_merge(x, kl_part[int64_t(i) * kl_parts + j]);
+      const float v = kl_value(x);
+      kl[i] = v;
+      skl += v;
+    }
   }
   const int K = B - 1;
   if (labels != nullptr) {
-    for (int i = threadIdx.x; i < n_seq * K; i += kKlThreads) {
+    for (int i = threadIdx.x; i < n_seq * K; i += kFinishThreads) {
       const int64_t s = i / K, k = i - s * K + 1;
-      const int64_t r = s * B + k;
-      const float v = zlse[r] - zl[r * ld + labels[i]];
+      const float at = zl[(s * B + k) * ld + labels[i]];
+      LseState x = ce_part[int64_t(i) * ce_parts];
+#pragma unroll 8
+      for (int j = 1; j < ce_parts; ++j) lse_merge(x, ce_part[int64_t(i) * ce_parts + j]);
+      const float v = x.m + logf(x.s) - at;
       if (ce != nullptr) ce[i] = v;
       sce += v;
     }
   }
   skl = wave_sum(skl);
   sce = wave_sum(sce);
-  if ((threadIdx.x & 63) == 0) {
-    sh[0][threadIdx.x >> 6] = skl;
-    sh[1][threadIdx.x >> 6] = sce;
+  if (lane == 0) {
+    sh[0][wid] = skl;
+    sh[1][wid] = sce;
   }
   __syncthreads();
   if (threadIdx.x == 0 && loss != nullptr) {
     float a = 0.f, c = 0.f;
-    for (int w = 0; w < kKlThreads / 64; ++w) {
+    for (int w = 0; w < W; ++w) {
       a += sh[0][w];
       c += sh[1][w];
     }
@@ -156,67 +324,60 @@ kl_finish_kernel(const KlState* __restrict__ part, int n_parts, int n_seq, int P
   }
 }
 
-__global__ void fill_u64_kernel(unsigned long long* p, int64_t n) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0ull;
-}
-
-static int kl_parts(int64_t rows, int V, int& chunk) {
+// Parts of a row of V columns and the columns of each (whole groups of eight): four
+// workgroups per CU over all rows, at least 2048 columns each.
+static int row_parts(int64_t rows, int V, int& chunk) {
   const int64_t want = (4 * int64_t(device_cu_count()) + rows - 1) / (rows > 0 ? rows : 1);
   const int max_parts = (V + 2047) / 2048;
-  int np = int(want < 1 ? 1 : (want > max_parts ? max_parts : want));
-  chunk = (V + np - 1) / np;
+  const int np = int(want < 1 ? 1 : (want > max_parts ? max_parts : want));
+  chunk = ((V + np - 1) / np + 7) / 8 * 8;
   return (V + chunk - 1) / chunk;
 }
 
 static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t kl_ws_bytes(int n_seq, int B, int P, int d, int V, bool bf16) {
-  const size_t R = size_t(n_seq) * P, M = size_t(n_seq) * B;
+  const size_t R = size_t(n_seq) * P, C = size_t(n_seq) * (B - 1);
   int ch;
-  const int np = kl_parts(int64_t(R), V, ch);
-  return al256(R * d * (bf16 ? 2 : 4)) + al256(R * 8) + al256(R * 4) + al256(R * size_t(V) * 4) +
-         al256(R * np * sizeof(KlState)) + al256(M * 4) + al256(sample_parts_bytes(int64_t(M), V));
+  const size_t np = size_t(row_parts(int64_t(R), V, ch)), nc = size_t(row_parts(int64_t(C), V, ch));
+  return al256(R * d * (bf16 ? 2 : 4)) + al256(R * 8) + al256(R * size_t(V) * 4) +
+         al256(R * np * sizeof(KlState)) + al256(C * nc * sizeof(LseState));
 }
 
 hipError_t launch_kl_forward(bool bf16, const void* H_pos, int m, const float* gamma, float eps,
                              const void* W_lm, int d, int V, const float* zl, int64_t ld, int B,
                              const int32_t* labels, int n_seq, int P, float T, float alpha,
                              float* kl, float* ce, float* loss, void* ws, hipStream_t s) {
-  const int64_t R = int64_t(n_seq) * P, M = int64_t(n_seq) * B;
+  const int64_t R = int64_t(n_seq) * P, C = int64_t(n_seq) * (B - 1);
   char* p = static_cast<char*>(ws);
   void* th = p;                       p += al256(size_t(R) * d * (bf16 ? 2 : 4));
   auto* keys = reinterpret_cast<unsigned long long*>(p); p += al256(size_t(R) * 8);
-  auto* am = reinterpret_cast<int32_t*>(p);             p += al256(size_t(R) * 4);
   auto* tl = reinterpret_cast<float*>(p);               p += al256(size_t(R) * V * 4);
-  int ch;
-  const int np = kl_parts(R, V, ch);
+  int kch, cch;
+  const int np = row_parts(R, V, kch), nc = row_parts(C, V, cch);
   auto* part = reinterpret_cast<KlState*>(p);           p += al256(size_t(R) * np * sizeof(KlState));
-  auto* zlse = reinterpret_cast<float*>(p);             p += al256(size_t(M) * 4);
-  void* rs_ws = p;
+  auto* cpart = reinterpret_cast<LseState*>(p);
+  const bool vec = (reinterpret_cast<uintptr_t>(H_pos) & 15u) == 0;
   if (bf16)
-    hipLaunchKernelGGL(pool_norm_kernel<bf16_t>, dim3(unsigned(R)), dim3(kKlThreads), 0, s,
-                       static_cast<const bf16_t*>(H_pos), m, d, gamma, eps, static_cast<bf16_t*>(th));
+    hipLaunchKernelGGL(pool_norm_kernel<bf16_t>, dim3(unsigned(R)), dim3(kPoolThreads), 0, s,
+                       static_cast<const bf16_t*>(H_pos), m, d, vec, gamma, eps,
+                       static_cast<bf16_t*>(th));
   else
-    hipLaunchKernelGGL(pool_norm_kernel<float>, dim3(unsigned(R)), dim3(kKlThreads), 0, s,
-                       static_cast<const float*>(H_pos), m, d, gamma, eps, static_cast<float*>(th));
+    hipLaunchKernelGGL(pool_norm_kernel<float>, dim3(unsigned(R)), dim3(kPoolThreads), 0, s,
+                       static_cast<const float*>(H_pos), m, d, vec, gamma, eps,
+                       static_cast<float*>(th));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fill_u64_kernel, dim3(unsigned((R + 255) / 256)), dim3(256), 0, s, keys, R);
+  // Only the logits are used: the argmax keys stay unread, whatever they held before.
+  e = launch_lm_head_keys(bf16, th, W_lm, R, d, V, keys, tl, s);
+  if (e != hipSuccess) return e;
+  const int64_t pair_wgs = R * np, wgs = pair_wgs + (labels != nullptr ? C * nc : 0);
+  hipLaunchKernelGGL(kl_pass_kernel, dim3(unsigned(wgs)), dim3(kKlThreads), 0, s, tl, zl, ld, B, P,
+                     V, pair_wgs, np, kch, nc, cch, 1.f / T, part, cpart);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = launch_lm_head(bf16, th, W_lm, R, d, V, keys, am, nullptr, tl, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kl_pass_kernel, dim3(unsigned(R), unsigned(np)), dim3(kKlThreads), 0, s, tl,
-                     zl, ld, B, P, V, ch, np, 1.f / T, part);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (labels != nullptr) {
-    e = launch_row_softmax(zl, M, V, ld, 1.f, false, 0, 0, nullptr, zlse, rs_ws, s);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kl_finish_kernel, dim3(1), dim3(kKlThreads), 0, s, part, np, n_seq, P, B, zl,
-                     ld, zlse, labels, T, alpha, kl, ce, loss);
+  hipLaunchKernelGGL(kl_finish_kernel, dim3(1), dim3(kFinishThreads), 0, s, part, np, cpart, nc,
+                     n_seq, P, B, zl, ld, labels, T, alpha, kl, ce, loss);
   return hipGetLastError();
 }
 

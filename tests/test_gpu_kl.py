@@ -56,3 +56,26 @@ def test_full_size_blocks():
 
 def test_without_labels_and_p_equal_k():
     _case(3, 5, 4, 2, 128, 777, "bf16", 0.5, 0.2, seed=3, labels=False)
+
+
+@pytest.mark.parametrize("n,B,P,m,d,V,dtype", [(1, 2, 1, 1, 64, 9, "f32"), (2, 3, 2, 8, 192, 2057, "bf16"),
+                                               (5, 64, 3, 3, 64, 513, "f32"), (300, 4, 3, 2, 64, 4111, "bf16"),
+                                               (1, 8, 2, 4, 8192, 135003, "bf16")])
+def test_pass_edges(n, B, P, m, d, V, dtype):
+    """Rows of odd lengths (unaligned), parts of less than a group, rows finished by a thread
+    and by a wave, more parts than a wave has lanes, the narrowest and widest states."""
+    _case(n, B, P, m, d, V, dtype, 1.0, 0.1, seed=n + B)
+
+
+def test_unaligned_states():
+    """Residual paths that start at an address that is not a multiple of 16 bytes."""
+    n, B, P, m, d, V = 2, 4, 2, 3, 128, 640
+    g = torch.Generator(device="cuda").manual_seed(4)
+    H = torch.randn((n, P, m, d), generator=g, device="cuda").to(torch.bfloat16)
+    flat = torch.empty(H.numel() + 1, dtype=torch.bfloat16, device="cuda")
+    flat[1:] = H.view(-1)
+    w = hdf.pack_weight(torch.randn((V, d), generator=g, device="cuda").to(torch.bfloat16))
+    z = torch.randn((n * B, V), generator=g, device="cuda")
+    a = hdf.kl_forward(H, w, z, B=B, P=P)
+    b = hdf.kl_forward(flat[1:].view(n, P, m, d), w, z, B=B, P=P)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[2], b[2])
