@@ -11,13 +11,12 @@
 // one contiguous 16 KB run per 64-k step, and no weight byte passes through LDS.
 //
 // bf16 kernel: NW waves (4, 6 or 8), each owning TN 32-column blocks (1; 2 for the LM
-// head's 128-row weight stream; 4 for the matrix-core bound shapes) and all BM rows
+// head's 128-row weight stream and the ping-pong tiles) and all BM rows
 // (BM = 128, or 64 when M <= 64) of a 32*NW*TN-column tile.  The activation slice
 // (BM x 64) is shared through a double-buffered, padded LDS tile.  A ring of STAGES
 // K-steps of weights is in flight per wave; activations are fetched one step further
 // ahead than weights because memory counters complete in issue order.  The matrix-core
-// bound tiles (128 x 512, 4 waves of 4 x 4 blocks, one wave per SIMD) run the deep K loop
-// described at its code.
+// bound partial sums (more than 128 rows) run in gemm_deep.hip.
 // Split-K runs over gridDim.z; tiles are ordered so that the M-tiles of one weight
 // column block run on the same XCD back to back (its L2 serves the re-reads); in tall
 // matrix-core bound problems an XCD's concurrent tiles form 8 x 4 blocks of row and column
@@ -35,6 +34,7 @@
 #include <initializer_list>
 
 #include "common.hpp"
+#include "gemm_tile.hpp"
 #include "kernels.hpp"
 
 namespace hdf {
@@ -42,30 +42,6 @@ namespace hdf {
 constexpr int kBK = 64;        // K granularity of the bf16 tiles (K % kBK == 0)
 constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last half step is zero-filled)
 constexpr int kGroupRows = 8;  // row tiles per group in the tile order of tall problems
-
-__host__ __device__ __forceinline__ int64_t packed_index(int64_t n, int64_t k, int64_t K) {
-  return (((n >> 7) * (K >> 4) + (k >> 4)) * 4 + ((n >> 5) & 3)) * 512 +
-         ((n & 31) + 32 * ((k & 15) >> 3)) * 8 + (k & 7);
-}
-
-__device__ __forceinline__ int remap_tile(int bid, int total) {
-  // XCD-aware order: dispatch sends consecutive workgroups round-robin over the 8
-  // XCDs; give each XCD a contiguous run of tile ids (the M-tiles of one weight
-  // column block are consecutive ids).
-  const int per = total >> 3;
-  if (bid < (per << 3)) return (bid & 7) * per + (bid >> 3);
-  return bid;
-}
-
-__device__ __forceinline__ unsigned long long argmax_key(float v, int col) {
-  return (static_cast<unsigned long long>(f32_order_key(v)) << 32) |
-         static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<uint32_t>(col));
-}
-
-// Activation unit of the deep K loop in LDS: row r's four 16-byte chunks (8 of K each)
-// sit at chunk positions c ^ unit_swizzle(r), so that the row-wise stores (four threads
-// a row) and the fragment reads (32 rows, one chunk each) meet distinct banks.
-__device__ __forceinline__ int unit_swizzle(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 // TN: 32-column weight blocks per wave (1, 2 or 4).  Each activation fragment read from
 // LDS feeds TN matrix-core operations, so wider waves cut the LDS traffic per MFMA; the
@@ -77,18 +53,16 @@ __device__ __forceinline__ int unit_swizzle(int r) { return ((r >> 1) ^ (r >> 2)
 // PP: the ping-pong K loop (128 x 512 tiles, 8 waves of two blocks): the two waves of a
 // SIMD alternate between a memory phase and a compute phase.  The K/V and argmax
 // epilogues of the matrix-core bound shapes run on it.
-// DEEP: the K loop of the matrix-core bound partial-sum tiles (128 x 512, 4 waves of 4 x 4
-// blocks, one wave per SIMD, a STAGES-unit weight ring in registers).
 // T = float: the same tiles, rings and epilogues on v_mfma_f32_32x32x2_f32.  A K step is 128
 // bytes of every activation row in either type, so the fp32 step is 32 of K; a packed
 // 32 x 16 block is 32 bytes a lane (two loads), and lane l's eight values (row l%32, k
 // 8*(l/32)..+7) are the operands of eight MFMAs, each taking k pair (e, 8 + e).
 template <typename T, int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1),
-          bool PP = false, bool DEEP = false>
+          bool PP = false>
 __global__ void __launch_bounds__(NW * 64)
 gemm_kernel(GemmArgs p) {
   constexpr bool F32 = sizeof(T) == 4;
-  static_assert(!F32 || !(PP || DEEP || EPI == kEpiKV), "the matrix-core bound loops are bf16");
+  static_assert(!F32 || !(PP || EPI == kEpiKV), "the matrix-core bound loops are bf16");
   constexpr int THREADS = NW * 64;
   constexpr int TM = BM / 32;
   constexpr int NB = NW * TN;                     // 32-column blocks of a tile
@@ -104,7 +78,6 @@ gemm_kernel(GemmArgs p) {
   // ARGMAX epilogue's logits to stage the fp32 tile 128 columns at a time ([block][row]
   // [32 columns]), and by the ARGMAX epilogue's per-wave row maxima.
   constexpr size_t kMainLds = PP     ? size_t(4) * BM * (32 + 8) * sizeof(bf16_t)   // NBUF units
-                              : DEEP ? size_t(2) * BM * 32 * sizeof(bf16_t)          // two K units
                                      : size_t(2) * BM * LDA * sizeof(T);
   constexpr size_t kEpiLds = (EPI != kEpiPartial)
       ? size_t(4) * BM * LDC * sizeof(float) + (EPI == kEpiKV ? size_t(2) * BM * sizeof(int) : 0)
@@ -132,7 +105,7 @@ gemm_kernel(GemmArgs p) {
   }
   const int mt = (p.M + BM - 1) / BM;
   int n_tile = tile / mt, m_tile = tile % mt;
-  if ((PP || DEEP) && mt > kGroupRows) {
+  if (PP && mt > kGroupRows) {
     // Tall problems (the cold context projection): consecutive tile ids walk a group of
     // kGroupRows row tiles, then the next column block, so the 32 tiles an XCD runs at
     // once are 8 row tiles x 4 column blocks and share their activation and weight slices
@@ -280,110 +253,6 @@ gemm_kernel(GemmArgs p) {
         if (u + j < nu) unit(u + j, j);
       if (grp == 0) __syncthreads();   // group 0 ends one phase later
     }
-  } else if constexpr (DEEP) {
-    // One wave per SIMD.  Each wave owns all 128 rows and one 128-row weight group (4 x 4
-    // blocks of 32 x 32), so every activation fragment read from LDS feeds four MFMAs and
-    // the 512 accumulators fill the accumulation registers.  A unit is 32 of K (two MFMA
-    // sub-steps).  The weights of a unit (8 KB a wave, 1 KB per load) go straight into a
-    // ring of R register slots, issued D = R - 1 units before their MFMAs.  The
-    // activations come through two swizzled LDS unit buffers: a thread stores its share
-    // of unit u+1 in the first half of unit u, one workgroup barrier follows, and the
-    // fragments of unit u+1's first sub-step are read during the second half, those of its
-    // second sub-step during the first half of unit u+1.  Loads are issued in the order
-    // they are waited for (the activations of unit u+D+1, then the weights of unit u+D),
-    // so the in-order load counter never makes one wait for the other.
-    static_assert(BM == 128 && NW == 4 && TN == 4, "deep tiles are 128 x 512, 4 waves of 4 x 4 blocks");
-    constexpr int UK = 32;
-    constexpr int R = STAGES;
-    constexpr int D = R - 1;
-    typedef bf16_t UTile[BM * UK];
-    UTile* Au = reinterpret_cast<UTile*>(smem);
-    const int nu = nk * (kBK / UK);
-    const int64_t ku0 = int64_t(kt_begin) * (kBK / UK);
-    // Activation staging: 512 chunks of 16 bytes per unit, thread tid moves chunks tid and
-    // tid + 256 (row q/4, chunk q%4).  Rows past M are clamped, units past the end re-read
-    // the last one; neither is ever used.
-    const bf16_t* a_src[2];
-    int a_lds[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int q = tid + 256 * j, row = q >> 2, c = q & 3;
-      a_src[j] = A + int64_t(min(m0 + row, p.M - 1)) * p.lda + c * 8;
-      a_lds[j] = row * UK + ((c ^ unit_swizzle(row)) * 8);
-    }
-    // Fragment of sub-step ss, row block i: lane l reads row 32i + l%32, chunk 2ss + l/32.
-    const int fr = lane & 31;
-    int f_off[2];
-#pragma unroll
-    for (int ss = 0; ss < 2; ++ss) f_off[ss] = fr * UK + (((2 * ss + (lane >> 5)) ^ unit_swizzle(fr)) * 8);
-    auto a_load = [&](int u, u32x4* dst) {
-      const int64_t k = (ku0 + min(u, nu - 1)) * UK;
-      dst[0] = ld16(a_src[0] + k);
-      dst[1] = ld16(a_src[1] + k);
-    };
-    auto a_store = [&](const u32x4* src, int buf) {
-      *reinterpret_cast<u32x4*>(&Au[buf][a_lds[0]]) = src[0];
-      *reinterpret_cast<u32x4*>(&Au[buf][a_lds[1]]) = src[1];
-    };
-    // Units past the end are never used: their loads read the activations' first 16
-    // bytes (in L2) instead of the weights.
-    auto b_load = [&](int u, u32x4 (*dst)[TN]) {
-      const bool live = u < nu;
-      const int64_t kb = (ku0 + (live ? u : 0)) * (UK / 16);
-#pragma unroll
-      for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-          dst[ss][tn] = ld16(live ? Bw[tn] + (kb + ss) * 4 * 512 : A);
-    };
-    auto frag = [&](int buf, int ss, int i) {
-      return *reinterpret_cast<const bf16x8_t*>(&Au[buf][f_off[ss] + 32 * i * UK]);
-    };
-    if (nu > 0) {
-      u32x4 rb[R][2][TN];
-      u32x4 ra[R][2];
-      a_load(0, ra[0]);
-#pragma unroll
-      for (int x = 0; x < D; ++x) {
-        a_load(x + 1, ra[(x + 1) % R]);
-        b_load(x, rb[x]);
-      }
-      a_store(ra[0], 0);
-      lds_barrier();
-      bf16x8_t f0[TM], f1[TM];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) f0[i] = frag(0, 0, i);
-      // Unit u in ring slot s = u % R.
-      auto unit = [&](int u, int s) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) f1[i] = frag(u & 1, 1, i);
-        a_store(ra[(u + 1) % R], (u + 1) & 1);
-        a_load(u + D + 1, ra[(u + D + 1) % R]);
-        b_load(u + D, rb[(s + D) % R]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-            acc[i][tn] = mma(f0[i], __builtin_bit_cast(bf16x8_t, rb[s][0][tn]), acc[i][tn]);
-        lds_barrier();
-#pragma unroll
-        for (int i = 0; i < TM; ++i) f0[i] = frag((u + 1) & 1, 0, i);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-            acc[i][tn] = mma(f1[i], __builtin_bit_cast(bf16x8_t, rb[s][1][tn]), acc[i][tn]);
-      };
-      int u = 0;
-      for (; u + R <= nu; u += R) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) unit(u + j, j);
-      }
-#pragma unroll
-      for (int j = 0; j < R; ++j)
-        if (u + j < nu) unit(u + j, j);
-    }
-    lds_barrier();   // the epilogues reuse LDS
   } else if (nk > 0) {
     u32x4 ra[STAGES][A_CH];
     u32x4 rb[STAGES][TN * 4];
@@ -754,19 +623,6 @@ __global__ void pack_weight_kernel(const T* __restrict__ src, T* __restrict__ ds
 
 // ---------------------------------------------------------------------------- host side
 
-// Matrix-core bound tiles: 128 x 512 in the deep K loop, 4 waves of 4 x 4 blocks with a
-// 4-unit weight ring (3 or 4 units measured the same; the register file holds no more).
-constexpr int kDeepWaves = 4, kDeepBlocks = 4, kDeepRing = 4;
-
-template <int EPI>
-static void launch_bf16_deep(const GemmArgs& a, int splits, hipStream_t s) {
-  constexpr int BN = 32 * kDeepWaves * kDeepBlocks;
-  const int tiles = ((a.M + 127) / 128) * ((a.N + BN - 1) / BN) +
-                    ((a.M2 + 127) / 128) * ((a.N2 + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, kDeepWaves, kDeepRing, EPI, kDeepBlocks, false, false, true>),
-                     dim3(tiles, 1, splits), dim3(kDeepWaves * 64), 0, s, a);
-}
-
 template <int NW, int TN, int STAGES = 4, bool NT = (TN == 1)>
 static void launch_bf16_partial(const GemmArgs& a, int splits, hipStream_t s) {
   const int BM = (a.M <= 64 && a.M2 <= 64) ? 64 : 128;
@@ -842,9 +698,8 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
                                   hipStream_t s) {
   if (bf16) {
     if (epi == kEpiPartial) {
-      if (plan.tn == kDeepBlocks) {
-        launch_bf16_deep<kEpiPartial>(a, plan.splits, s);
-      } else if (!plan.nt) {
+      if (plan.tn > 1) return launch_gemm_deep(a, plan, s);
+      if (!plan.nt) {
         launch_bf16_partial<8, 1, 4, false>(a, plan.splits, s);
       } else if (plan.nw == 8) {
         launch_bf16_partial<8, 1>(a, plan.splits, s);
@@ -901,32 +756,9 @@ GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
   // the CUs best without exceeding them; ties go to fewer splits (less partial
   // traffic) and then to more waves (more bytes in flight per CU).  Every split keeps
   // at least 8 K-steps.
-  // Above 128 rows the products are matrix-core bound: waves then own two column blocks
-  // each, which halves the LDS traffic per MFMA, and fetch the weights through the caches
-  // so that the other row tiles find them in L2 (measured at M = 1024: down 90 -> 71 us,
-  // the cold context projection 1182 -> 800 us).
+  // Above 128 rows the products are matrix-core bound (gemm_deep.hip).
   const int BM = (M <= 64 && M2 <= 64) ? 64 : 128;
-  const bool mfma_bound = M > 128 || M2 > 128;
-  if (mfma_bound) {
-    // Matrix-core bound: the deep 128 x 512 tiles.  The time is about the
-    // number of rounds of workgroups over the CUs times the K range of one workgroup,
-    // plus the fp32 partials of every extra split (charged 15% each): pick the split
-    // that minimises rounds / splits * (1 + 0.15 (splits - 1)).  At 1024 rows: gate/up
-    // 2 splits (197 -> 185 us), down 4 (86 -> 71 us), QKV 1.
-    const int tiles = ((M + BM - 1) / BM) * ((N + 511) / 512) +
-                      ((M2 + BM - 1) / BM) * ((N2 + 511) / 512);
-    int best_s = 1;
-    double best_t = 1e30;
-    for (int sp = 1; sp <= 8; ++sp) {
-      if (sp > 1 && nk / sp < 8) break;
-      const double t = double((tiles * sp + ncu - 1) / ncu) / sp * (1.0 + 0.15 * (sp - 1));
-      if (t < best_t - 1e-9) {
-        best_t = t;
-        best_s = sp;
-      }
-    }
-    return GemmPlan{kDeepWaves, best_s, kDeepBlocks};
-  }
+  if (M > 128 || M2 > 128) return deep_plan(M, N, M2, N2, K);
   return plan_stream(BM, M, N, M2, N2, nk, ncu, {4, 6, 8});
 }
 
@@ -1003,10 +835,7 @@ hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int 
                           GemmPlan plan, const int32_t* plan_pos, const int32_t* plan_row,
                           const float* rope_cs, void* kc, void* vtc, int64_t cap, hipStream_t s) {
   // 512-column tiles lie wholly in K or in V when d % 512 == 0.
-  // The matrix-core bound plan with one K split; the K/V epilogue runs on the ping-pong
-  // tiles of the same 512 columns.
-  if (plan.tn != kDeepBlocks || plan.nw != kDeepWaves || plan.splits != 1 || (hd != 64 && hd != 128) ||
-      d % 512 != 0)
+  if (plan.tn < 2 || plan.splits != 1 || (hd != 64 && hd != 128) || d % 512 != 0)
     return hipErrorInvalidValue;
   if (M <= 0) return hipSuccess;
   GemmArgs a{};

@@ -1,0 +1,312 @@
+// The matrix-core bound tiles (bf16, more than 128 rows): C = A . W^T over the packed weight
+// layout described in gemm.hip, 4 waves of 16 blocks of 32 x 32, one wave per SIMD.  Two tile
+// shapes of the same area:
+//   TM = 4: 128 rows x 512 columns, a wave owns all rows and one 128-row weight group;
+//   TM = 8: 256 rows x 256 columns, a wave owns all rows and half a weight group.
+//
+// K loop.  A unit is 32 of K, two sub-steps of 16 MFMAs, which keep the matrix core of a
+// SIMD busy for 1024 cycles; the sixteen accumulators fill the accumulation registers.
+//   Weights: 32 KB (TM = 4) or 16 KB (TM = 8) a unit and workgroup straight into a register
+//     ring of R units, issued R - 1 units before their use.
+//   Activations: loaded two units (64 of K, whole 128-byte lines) at a time, stored into
+//     swizzled LDS unit buffers CU units before their use; one workgroup barrier per CU units.
+//     A wave reads the fragments of a sub-step during the sub-step before it.
+// With one wave per SIMD nothing hides a wait, so every load, LDS access and MFMA is pinned
+// in the order it is written here (a scheduling fence after each): the compiler's own order
+// sank the fragment reads to their uses, an exposed LDS round trip every four MFMAs.
+// Addresses cost no vector instructions: buffer loads with a per-lane offset computed once
+// and the unit in the scalar offset; the descriptors end at the operands' last row or unit,
+// so rows past M and units past K read as zero without a fetch.
+//
+// Measured alone (random operands, warm): 16384 x 4096 -> 8192 972 -> 815 us with fp32 stores,
+// 16384 x 16384 -> 4096 1878 -> 1520 us, 1024 x 4096 -> 24576 in two K splits 204 -> 180 us,
+// 1024 x 12288 -> 4096 in four 96 -> 81 us (before: compiler-ordered loop of the 128 x 512
+// tiles).  Copies without stores run at 1.40-1.52 PFLOP/s, without any load from memory in
+// the loop at 1.60-1.72, the MFMAs alone at 1.67-1.80 (the power limit on such data).
+#include "common.hpp"
+#include "gemm_tile.hpp"
+#include "kernels.hpp"
+
+namespace hdf {
+
+constexpr int kDeepThreads = 256;
+constexpr int kDeepRing = 4;     // weight units in the register ring
+// Row tiles of one group in the tile order of tall problems: consecutive tile ids walk four
+// row tiles of a column block, then the next column block, so that the 32 tiles an XCD runs
+// share activation and weight slices in its L2 (16384 x 4096 -> 8192: 4 row tiles 846 us, 8
+// 889, 2 887, 1 895; 16384 x 16384 -> 4096 within 1% from 1 to 4, 8 3% slower).  Up to eight
+// row tiles form one group, so that weights from HBM are fetched by all of them at once (1024
+// rows as eight tiles of 128: 24576 columns 193 us in one group, 207 in two).
+constexpr int kDeepGroup = 4;
+
+typedef __amdgpu_buffer_rsrc_t BufRsrc;
+__device__ __forceinline__ BufRsrc buf_rsrc(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 buf_ld16(BufRsrc r, int lane_off, int uniform_off) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, uniform_off, 0));
+}
+// Nothing moves across (the pinned order of the K loop).
+#define HDF_PIN() __builtin_amdgcn_sched_barrier(0)
+
+// 16-byte chunk c (8 of K) of a unit's row r sits at chunk c ^ unit_swizzle(r), so that the
+// stores (eight threads a row, four in each of two units) and the fragment reads (32 rows,
+// one chunk each) meet distinct banks.
+__device__ __forceinline__ int unit_swizzle(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
+
+template <int TM>
+struct DeepTile {
+  static constexpr int TN = 16 / TM;
+  static constexpr int BM = 32 * TM, BN = 128 * TN;
+  static constexpr int UK = 32;
+  static constexpr int CU = TM == 4 ? 4 : 2;            // units per barrier
+  static constexpr int NB = 2 * CU;                     // LDS unit buffers
+  static constexpr int UB = BM * UK + 64;               // elements between them (128 bytes apart
+                                                        // in the banks: a pair's stores meet)
+  static constexpr int PCH = BM * 64 * 2 / 16 / kDeepThreads;   // 16-byte chunks a thread and pair
+  static constexpr size_t kLds = size_t(NB) * UB * sizeof(bf16_t);
+};
+
+// acc[i][t] += rows 32i.. of the tile x columns of the wave's block t, over units ku0 ..
+// ku0 + nu - 1 (nu even, at least 2).  SWAP: the transposed product (the weights as the A
+// operand).  On return every wave has left the loop's last LDS read behind, not a barrier.
+template <int TM, bool SWAP>
+__device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const BufRsrc ra_, int64_t lda,
+                                          const BufRsrc rb_, int blk_off, int ku0, int nu,
+                                          bf16_t* lds) {
+  using Tl = DeepTile<TM>;
+  constexpr int TN = Tl::TN, UK = Tl::UK, CU = Tl::CU, NB = Tl::NB, UB = Tl::UB, PCH = Tl::PCH;
+  constexpr int R = kDeepRing, D = R - 1, AH = PCH / 2;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int bv = lane * 16 + blk_off;
+  int av[PCH], al[PCH];   // chunk q of a pair: row q/8, 16-byte column q%8 (unit q%8/4)
+#pragma unroll
+  for (int j = 0; j < PCH; ++j) {
+    const int q = tid + kDeepThreads * j, row = q >> 3, c = q & 7;
+    av[j] = row * int(lda) * 2 + c * 16;
+    al[j] = (c >> 2) * UB + row * UK + (((c & 3) ^ unit_swizzle(row)) * 8);
+  }
+  // Fragment of sub-step ss, row block i: lane l reads row 32i + l%32, chunk 2ss + l/32.
+  const int fr = lane & 31;
+  int fo[2];
+#pragma unroll
+  for (int ss = 0; ss < 2; ++ss) fo[ss] = fr * UK + (((2 * ss + (lane >> 5)) ^ unit_swizzle(fr)) * 8);
+  u32x4 rb[R][2][TN];
+  u32x4 ra[2][PCH];
+  const int np = nu / 2;
+  // Pairs past the end re-read the last one (never used); units past the end read zeros.
+  auto a_load = [&](int pr, int j, u32x4* dst) {
+    dst[j] = buf_ld16(ra_, av[j], (ku0 / 2 + min(pr, np - 1)) * 128);
+  };
+  auto b_load = [&](int u, int ss, int t, u32x4 (*dst)[TN]) {
+    dst[ss][t] = buf_ld16(rb_, bv + t * 1024, (ku0 + u) * 8192 + ss * 4096);
+  };
+  auto a_store = [&](const u32x4* src, int j, int buf) {
+    *reinterpret_cast<u32x4*>(&lds[buf * UB + al[j]]) = src[j];
+  };
+  auto frag = [&](int buf, int ss, int i) {
+    return *reinterpret_cast<const bf16x8_t*>(&lds[buf * UB + fo[ss] + 32 * i * UK]);
+  };
+  auto mma = [](bf16x8_t act, u32x4 w, f32x16_t c) {
+    const bf16x8_t wv = __builtin_bit_cast(bf16x8_t, w);
+    return SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, act, c, 0, 0, 0)
+                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(act, wv, c, 0, 0, 0);
+  };
+  // Prologue: the pairs of the first CU units into LDS (they are waited for first), the next
+  // pair and the first D units of weights in flight.
+  u32x4 first[CU / 2][PCH];
+#pragma unroll
+  for (int v = 0; v < CU / 2; ++v)
+#pragma unroll
+    for (int j = 0; j < PCH; ++j) a_load(v, j, first[v]);
+#pragma unroll
+  for (int j = 0; j < PCH; ++j) a_load(CU / 2, j, ra[0]);
+#pragma unroll
+  for (int x = 0; x < D; ++x)
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int t = 0; t < TN; ++t) b_load(x, ss, t, rb[x]);
+#pragma unroll
+  for (int v = 0; v < CU / 2; ++v)
+#pragma unroll
+    for (int j = 0; j < PCH; ++j) a_store(first[v], j, 2 * v);
+  lds_barrier();
+  bf16x8_t f0[TM], f1[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) f0[i] = frag(0, 0, i);
+  // Unit u, with j = u % U known at compile time.  During it: this unit's second fragments
+  // and the next unit's first ones, half of the pair CU units ahead into LDS, half of the
+  // loads of the pair after that one, the weights D units ahead; spread over the MFMAs.
+  constexpr int U = 2 * CU > R ? 2 * CU : R;
+  static_assert(U % R == 0 && U % NB == 0, "unit indexes are static over the unrolled units");
+  auto unit = [&](int u, int j) {
+    const int s = j % R, buf = j % NB, nbuf = (j + 1) % NB;
+    const int wbuf = ((j / 2 + CU / 2) * 2) % NB;
+    const int h = (j & 1) * AH, rs = (j / 2) & 1;
+    auto rd1 = [&](int i) { f1[i] = frag(buf, 1, i); HDF_PIN(); };
+    auto rd0 = [&](int i) { f0[i] = frag(nbuf, 0, i); HDF_PIN(); };
+    auto st = [&](int x) { a_store(ra[rs], h + x, wbuf); HDF_PIN(); };
+    auto la = [&](int x) { a_load((u >> 1) + CU / 2 + 1, h + x, ra[rs ^ 1]); HDF_PIN(); };
+    auto lb = [&](int ss, int t) { b_load(u + D, ss, t, rb[(s + D) % R]); HDF_PIN(); };
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if constexpr (TM == 4) {
+        if (k < 8 && k % 2 == 0) rd1(k / 2);
+        if (k < 12 && k % 3 == 1) lb(0, k / 3);
+        if (k == 9 || k == 11) st((k - 9) / 2);
+        if (k == 13 || k == 15) la((k - 13) / 2);
+      } else {
+        if (k % 2 == 0) rd1(k / 2);
+        if (k % 4 == 1) st(k / 4);
+        if (k % 4 == 3) la(k / 4);
+        if (k == 6 || k == 12) lb(0, (k - 6) / 6);
+      }
+      acc[k / TN][k % TN] = mma(f0[k / TN], rb[s][0][k % TN], acc[k / TN][k % TN]);
+      HDF_PIN();
+    }
+    if (j % CU == CU - 1) {
+      lds_barrier();
+      HDF_PIN();
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if constexpr (TM == 4) {
+        if (k < 8 && k % 2 == 0) rd0(k / 2);
+        if (k % 4 == 3) lb(1, k / 4);
+      } else {
+        if (k % 2 == 0) rd0(k / 2);
+        if (k == 5 || k == 11) lb(1, (k - 5) / 6);
+      }
+      acc[k / TN][k % TN] = mma(f1[k / TN], rb[s][1][k % TN], acc[k / TN][k % TN]);
+      HDF_PIN();
+    }
+  };
+  int u = 0;
+  for (; u + U <= nu; u += U) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) unit(u + j, j);
+  }
+#pragma unroll
+  for (int j = 0; j < U; ++j)
+    if (u + j < nu) unit(u + j, j);
+}
+
+template <int TM, int EPI>
+__global__ void __launch_bounds__(kDeepThreads, 1)
+gemm_deep_kernel(GemmArgs p) {
+  using Tl = DeepTile<TM>;
+  constexpr int TN = Tl::TN, BM = Tl::BM, BN = Tl::BN;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[Tl::kLds];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+  // Tiles of the first problem, then those of the optional second one.
+  const int tiles1 = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
+  int tile = remap_tile(blockIdx.x, gridDim.x);
+  if (tile >= tiles1) {
+    tile -= tiles1;
+    p.A = p.A2;
+    p.lda = p.lda2;
+    p.B = p.B2;
+    p.M = p.M2;
+    p.N = p.N2;
+    p.C = p.C2;
+  }
+  const int mt = (p.M + BM - 1) / BM, nt = (p.N + BN - 1) / BN;
+  const int group = mt <= 2 * kDeepGroup ? mt : kDeepGroup;
+  const int in_group = group * nt;
+  const int g = tile / in_group, first = g * group;
+  const int gm = min(mt - first, group);
+  const int gr = tile - g * in_group;
+  const int m_tile = first + gr % gm, n_tile = gr / gm;
+  const int m0 = m_tile * BM, n0 = n_tile * BN;
+
+  const int nk_all = p.K / 64;
+  const int z = blockIdx.z;
+  const int k0 = (nk_all * z) / gridDim.z, k1 = (nk_all * (z + 1)) / gridDim.z;
+  // This wave's 32-row weight blocks start at block blk0 of the packed weights (a group past
+  // the last one is clamped to it, and the columns it computes are never stored).
+  const int blk0 = (n_tile * 4 + wid) * TN;
+  const int grp = min(blk0 >> 2, ((p.N + 127) >> 7) - 1);
+  const bf16_t* A = static_cast<const bf16_t*>(p.A) + int64_t(m0) * p.lda;
+  const bf16_t* B = static_cast<const bf16_t*>(p.B) + int64_t(grp) * (p.K >> 4) * 2048;
+  const BufRsrc ra = buf_rsrc(A, int((int64_t(min(BM, p.M - m0) - 1) * p.lda + p.K) * 2));
+  const BufRsrc rb = buf_rsrc(B, k1 * 2 * 8192);
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
+  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
+  if (k1 > k0)
+    deep_loop<TM, false>(acc, ra, p.lda, rb, (blk0 & 3) * 1024, k0 * 2, (k1 - k0) * 2, lds);
+
+  // fp32 C (or split-K partial z at C + z*M*N) straight from the accumulators.
+  float* C = p.C + int64_t(z) * p.M * p.N;
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int col = n0 + 32 * (wid * TN + t) + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = m0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (row < p.M && col < p.N) C[int64_t(row) * p.N + col] = acc[i][t][r];
+      }
+  }
+}
+
+// ---------------------------------------------------------------------------- host side
+
+template <int TM, int EPI>
+static void launch_deep(const GemmArgs& a, int splits, hipStream_t s) {
+  using Tl = DeepTile<TM>;
+  const int tiles = ((a.M + Tl::BM - 1) / Tl::BM) * ((a.N + Tl::BN - 1) / Tl::BN) +
+                    ((a.M2 + Tl::BM - 1) / Tl::BM) * ((a.N2 + Tl::BN - 1) / Tl::BN);
+  hipLaunchKernelGGL((gemm_deep_kernel<TM, EPI>), dim3(tiles, 1, splits), dim3(kDeepThreads), 0, s, a);
+}
+
+hipError_t launch_gemm_deep(const GemmArgs& a, const GemmPlan& plan, hipStream_t s) {
+  if (plan.tn == DeepTile<4>::TN)
+    launch_deep<4, kEpiPartial>(a, plan.splits, s);
+  else
+    launch_deep<8, kEpiPartial>(a, plan.splits, s);
+  return hipGetLastError();
+}
+
+// The tile of the shape with fewer rounds of workgroups over the CUs, and the K split: the
+// time is about the number of rounds times the K range of one workgroup, plus the fp32
+// partials of every extra split (charged 15% each).  On ties the 256 x 256 tiles up to 2048
+// rows, where the weights come from HBM and half as many row tiles re-read them (1024 x 4096
+// -> 24576: 180 against 212 us; -> 129280 862 against 938; 1024 x 12288 -> 4096 82.5 against
+// 80.8), the 128 x 512 tiles above, whose fragments cost half the LDS reads (16384 x 4096 ->
+// 8192: 815 against 820 us, 16384 x 16384 -> 4096 1520 against 1553).
+GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
+  const int ncu = device_cu_count();
+  const int nk = K / 64;
+  auto tiles_of = [&](int bm, int bn) {
+    return int64_t((M + bm - 1) / bm) * ((N + bn - 1) / bn) + int64_t((M2 + bm - 1) / bm) * ((N2 + bn - 1) / bn);
+  };
+  const int64_t tiles[2] = {tiles_of(256, 256), tiles_of(128, 512)};
+  const bool tall = M > 2048 || M2 > 2048;
+  int best_s = 1, best_i = 0;
+  double best_t = 1e30;
+  for (int sp = 1; sp <= 8; ++sp) {
+    if (sp > 1 && nk / sp < 8) break;
+    for (int x = 0; x < 2; ++x) {
+      const int i = tall ? 1 - x : x;
+      const double t = double((tiles[i] * sp + ncu - 1) / ncu) / sp * (1.0 + 0.15 * (sp - 1));
+      if (t < best_t - 1e-9) {
+        best_t = t;
+        best_s = sp;
+        best_i = i;
+      }
+    }
+  }
+  return GemmPlan{4, best_s, best_i == 0 ? DeepTile<8>::TN : DeepTile<4>::TN};
+}
+
+}  // namespace hdf

@@ -72,7 +72,7 @@ int gemm_k_align(bool bf16);                       // K must be a multiple of th
 // 4, 6 or 8) and the number of K splits.
 struct GemmPlan {
   int nw, splits;
-  int tn = 1;       // 32-column blocks per wave (4 for the matrix-core bound shapes)
+  int tn = 1;       // 32-column blocks per wave (2 or 4: the tiles of gemm_deep.hip)
   bool nt = true;   // one-block waves: weights streamed past the caches
 };
 GemmPlan gemm_plan(bool bf16, int M, int N, int K);
@@ -81,6 +81,9 @@ GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K);
 // Two problems of the same K in one launch where the first one's row tiles (up to 256
 // rows) share weight columns: weights fetched through L2 (8 waves of one block).
 GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K);
+// Matrix-core bound bf16 problems (gemm_deep.hip): the plan, and fp32 partials by it.
+GemmPlan deep_plan(int M, int N, int M2, int N2, int K);
+hipError_t launch_gemm_deep(const GemmArgs& a, const GemmPlan& plan, hipStream_t s);
 size_t packed_weight_elems(int N, int K);          // rows rounded up to 128
 hipError_t launch_pack_weight(bool bf16, const void* src, void* dst, int N, int K, hipStream_t s);
 // C[z][M][N] (fp32) = A[M][K] . W[N][K]^T over the z-th of `splits` K ranges; W packed.

@@ -72,3 +72,11 @@ def test_fp32_k_steps(n, m, d):
     """fp32 tiles with whole and half last K steps (m*d a multiple of 16 only), K below one
     step, K splits, and row counts around 32, 64 and 128."""
     _case(n, m, d, "f32", n + m, n % 2 == 1)
+
+
+@pytest.mark.parametrize("n,m,d", [(129, 3, 64), (256, 5, 64), (255, 1, 576), (513, 7, 192), (1025, 2, 1088),
+                                   (2049, 3, 320), (2177, 5, 64), (4100, 1, 704)])
+def test_matrix_core_tiles(n, m, d):
+    """The matrix-core bound tiles around their row and column edges, both tile shapes, and K
+    of one, three, five, seven and more 64-K steps (a part of the loop's unrolled units)."""
+    _case(n, m, d, "bf16", n + m, n % 2 == 0)
