@@ -11,16 +11,14 @@
 // one contiguous 16 KB run per 64-k step, and no weight byte passes through LDS.
 //
 // bf16 kernel: NW waves (4, 6 or 8), each owning TN 32-column blocks (1; 2 for the LM
-// head's 128-row weight stream and the ping-pong tiles) and all BM rows
-// (BM = 128, or 64 when M <= 64) of a 32*NW*TN-column tile.  The activation slice
+// head's weight stream of up to 128 rows) and all BM rows (BM = 128, or 64 when M <= 64;
+// 192 for the LM head's one-pass tiles) of a 32*NW*TN-column tile.  The activation slice
 // (BM x 64) is shared through a double-buffered, padded LDS tile.  A ring of STAGES
 // K-steps of weights is in flight per wave; activations are fetched one step further
 // ahead than weights because memory counters complete in issue order.  The matrix-core
-// bound partial sums (more than 128 rows) run in gemm_deep.hip.
+// bound problems (more than 128 rows; the LM head above 192) run in gemm_deep.hip.
 // Split-K runs over gridDim.z; tiles are ordered so that the M-tiles of one weight
-// column block run on the same XCD back to back (its L2 serves the re-reads); in tall
-// matrix-core bound problems an XCD's concurrent tiles form 8 x 4 blocks of row and column
-// tiles instead.
+// column block run on the same XCD back to back (its L2 serves the re-reads).
 //
 // Epilogues:
 //   PARTIAL  fp32 C (or split-K partial z at C + z*M*N) straight from registers
@@ -41,7 +39,6 @@ namespace hdf {
 
 constexpr int kBK = 64;        // K granularity of the bf16 tiles (K % kBK == 0)
 constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last half step is zero-filled)
-constexpr int kGroupRows = 8;  // row tiles per group in the tile order of tall problems
 
 // TN: 32-column weight blocks per wave (1, 2 or 4).  Each activation fragment read from
 // LDS feeds TN matrix-core operations, so wider waves cut the LDS traffic per MFMA; the
@@ -50,19 +47,14 @@ constexpr int kGroupRows = 8;  // row tiles per group in the tile order of tall 
 // NT: fetch the weights with non-temporal loads (they stream past the caches).  Right
 // when one row tile reads every weight byte once; with several row tiles the others
 // re-read the weights from L2, so they are fetched through the caches.
-// PP: the ping-pong K loop (128 x 512 tiles, 8 waves of two blocks): the two waves of a
-// SIMD alternate between a memory phase and a compute phase.  The K/V and argmax
-// epilogues of the matrix-core bound shapes run on it.
 // T = float: the same tiles, rings and epilogues on v_mfma_f32_32x32x2_f32.  A K step is 128
 // bytes of every activation row in either type, so the fp32 step is 32 of K; a packed
 // 32 x 16 block is 32 bytes a lane (two loads), and lane l's eight values (row l%32, k
 // 8*(l/32)..+7) are the operands of eight MFMAs, each taking k pair (e, 8 + e).
-template <typename T, int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1),
-          bool PP = false>
+template <typename T, int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1)>
 __global__ void __launch_bounds__(NW * 64)
 gemm_kernel(GemmArgs p) {
   constexpr bool F32 = sizeof(T) == 4;
-  static_assert(!F32 || !(PP || EPI == kEpiKV), "the matrix-core bound loops are bf16");
   constexpr int THREADS = NW * 64;
   constexpr int TM = BM / 32;
   constexpr int NB = NW * TN;                     // 32-column blocks of a tile
@@ -73,15 +65,11 @@ gemm_kernel(GemmArgs p) {
   constexpr int A_CHUNKS = BM * BK / VEC;          // 16-byte chunks of an activation step
   constexpr int A_CH = (A_CHUNKS + THREADS - 1) / THREADS;
   constexpr int LDC = 33;                         // padded row of a wave's 32 columns
-  static_assert(EPI == kEpiPartial || NB % 4 == 0, "argmax and K/V tiles are whole 128-column slabs");
-  // LDS: the activation buffers, reused after the K loop by the K/V epilogue and the
-  // ARGMAX epilogue's logits to stage the fp32 tile 128 columns at a time ([block][row]
-  // [32 columns]), and by the ARGMAX epilogue's per-wave row maxima.
-  constexpr size_t kMainLds = PP     ? size_t(4) * BM * (32 + 8) * sizeof(bf16_t)   // NBUF units
-                                     : size_t(2) * BM * LDA * sizeof(T);
-  constexpr size_t kEpiLds = (EPI != kEpiPartial)
-      ? size_t(4) * BM * LDC * sizeof(float) + (EPI == kEpiKV ? size_t(2) * BM * sizeof(int) : 0)
-      : 0;
+  static_assert(EPI == kEpiPartial || NB % 4 == 0, "argmax tiles are whole 128-column slabs");
+  // LDS: the activation buffers, reused after the K loop by the ARGMAX epilogue to stage the
+  // logits 128 columns at a time ([block][row][32 columns]) and for its per-wave row maxima.
+  constexpr size_t kMainLds = size_t(2) * BM * LDA * sizeof(T);
+  constexpr size_t kEpiLds = EPI != kEpiPartial ? size_t(4) * BM * LDC * sizeof(float) : 0;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kMainLds > kEpiLds ? kMainLds : kEpiLds];
   typedef T ATile[BM][LDA];
   ATile* As = reinterpret_cast<ATile*>(smem);
@@ -104,22 +92,7 @@ gemm_kernel(GemmArgs p) {
     p.C = p.C2;
   }
   const int mt = (p.M + BM - 1) / BM;
-  int n_tile = tile / mt, m_tile = tile % mt;
-  if (PP && mt > kGroupRows) {
-    // Tall problems (the cold context projection): consecutive tile ids walk a group of
-    // kGroupRows row tiles, then the next column block, so the 32 tiles an XCD runs at
-    // once are 8 row tiles x 4 column blocks and share their activation and weight slices
-    // in its L2 (with row tiles of one column block only, every activation slice missed):
-    // 16384 x 4096 x 8192 with the K/V epilogue 1.58 -> 1.55 ms per cold step, the
-    // 540K-row cold ragged step 46.5 -> 44.3 ms.
-    const int nt = (p.N + BN - 1) / BN;
-    const int in_group = kGroupRows * nt;
-    const int g = tile / in_group, first = g * kGroupRows;
-    const int gm = min(mt - first, kGroupRows);
-    const int r = tile - g * in_group;
-    m_tile = first + r % gm;
-    n_tile = r / gm;
-  }
+  const int n_tile = tile / mt, m_tile = tile % mt;
   const int m0 = m_tile * BM, n0 = n_tile * BN;
 
   const int nk_all = (p.K + BK - 1) / BK;
@@ -166,94 +139,7 @@ gemm_kernel(GemmArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][tn][r] = 0.f;
 
-  if constexpr (PP) {
-    // Waves 4-7 (group 1) run one phase behind waves 0-3 (group 0); the two waves of a
-    // SIMD come one from each group.  In its memory phase a wave reads the activation
-    // fragments of its next unit (32 of K) from LDS, stores its share of a later unit's
-    // activations into LDS and issues the weight loads of the unit D ahead; in its
-    // compute phase it runs the unit's 16 MFMAs from registers only.  A workgroup
-    // barrier ends every phase, so while one wave of a SIMD computes, the other loads.
-    static_assert(BM == 128 && NW == 8 && TN == 2, "ping-pong tiles are 128 x 512, 8 waves");
-    constexpr int UK = 32;                   // K of one unit (two MFMA sub-steps)
-    constexpr int LDU = UK + 8;              // padded LDS row of a unit (bf16 elements)
-    constexpr int NBUF = 4;                  // LDS buffers of activation units
-    constexpr int D = 2;                     // weight units in flight ahead of their use
-    constexpr int NR = D + 1;
-    static_assert(size_t(NBUF) * BM * LDU * sizeof(bf16_t) <= sizeof(smem), "LDS");
-    typedef bf16_t UTile[BM][LDU];
-    UTile* Au = reinterpret_cast<UTile*>(smem);
-    const int nu = nk * (kBK / UK);
-    const int64_t ku0 = int64_t(kt_begin) * (kBK / UK);
-    const int grp = wid >> 2;
-    // Activation staging: thread tid moves row tid/4, 16-byte chunk tid%4 of each unit
-    // (512 threads x 16 B = one 128 x 32 unit).  Rows past M are clamped, units past the
-    // end re-read the last one; neither is ever used.
-    const bf16_t* a_src = A + int64_t(min(m0 + (tid >> 2), p.M - 1)) * p.lda + (tid & 3) * 8;
-    auto a_load = [&](int u) { return ld16(a_src + (ku0 + min(u, nu - 1)) * UK); };
-    auto a_store = [&](const u32x4& v, int u) {
-      *reinterpret_cast<u32x4*>(&Au[u % NBUF][tid >> 2][(tid & 3) * 8]) = v;
-    };
-    // Units past the end are never used: their loads read the activations' first 16
-    // bytes (in L2) instead of the weights again (see load_b below).
-    auto b_load = [&](int u, u32x4* dst) {
-      const bool live = u < nu;
-      const int64_t kb = (ku0 + (live ? u : 0)) * (UK / 16);
-#pragma unroll
-      for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-          dst[ss * TN + tn] = ld16(live ? Bw[tn] + (kb + ss) * 4 * 512 : A);
-    };
-    const int arow = lane & 31;
-    const int kof = 8 * (lane >> 5);
-    if (nu > 0) {
-      u32x4 rb[NR][2 * TN];
-      u32x4 areg = a_load(0);
-      a_store(areg, 0);
-      areg = a_load(1);
-      a_store(areg, 1);
-      areg = a_load(2);
-#pragma unroll
-      for (int j = 0; j < D; ++j) b_load(j, rb[j]);
-      __syncthreads();
-      if (grp == 1) __syncthreads();   // group 1 starts one phase behind
-      // Unit u: buffer u % NBUF holds its activations (written during the memory phases
-      // of unit u-2 by both groups); rb[slot] its weights (loaded D units earlier).
-      auto unit = [&](int u, int slot) {
-        bf16x8_t af[2][TM];
-#pragma unroll
-        for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-            af[ss][i] = *reinterpret_cast<const bf16x8_t*>(
-                &Au[u % NBUF][arow + 32 * i][ss * 16 + kof]);
-        a_store(areg, u + 2);
-        areg = a_load(u + 3);
-        b_load(u + D, rb[(slot + D) % NR]);
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-              acc[i][tn] = mma(af[ss][i], __builtin_bit_cast(bf16x8_t, rb[slot][ss * TN + tn]),
-                               acc[i][tn]);
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-      };
-      int u = 0;
-      for (; u + NR <= nu; u += NR) {
-#pragma unroll
-        for (int j = 0; j < NR; ++j) unit(u + j, j);
-      }
-#pragma unroll
-      for (int j = 0; j < NR; ++j)
-        if (u + j < nu) unit(u + j, j);
-      if (grp == 0) __syncthreads();   // group 0 ends one phase later
-    }
-  } else if (nk > 0) {
+  if (nk > 0) {
     u32x4 ra[STAGES][A_CH];
     u32x4 rb[STAGES][TN * 4];
     // Activation chunk c of a K-step: row c/8, 16-byte column c%8.  Rows past M are
@@ -376,127 +262,6 @@ gemm_kernel(GemmArgs p) {
           const int row = m0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           if (row < p.M && col < p.N) C[int64_t(row) * p.N + col] = acc[i][tn][r];
         }
-    }
-  } else if constexpr (EPI == kEpiKV) {
-    // Context K/V rows straight into the cache, one 128-column slab (whole heads) of the
-    // tile at a time through LDS ([block][row][column of the block]): K columns get RoPE
-    // at the row's position (pairs i, i + hd/2 of a head) and go to the key tile layout,
-    // four consecutive dims per store; V columns go to the transposed value layout with
-    // consecutive threads on consecutive rows of one dim.  The same fp32 values and the
-    // same rounding as the partial-sum path and its epilogue kernel.
-    float* Cs = reinterpret_cast<float*>(smem);
-    // The tile's row table: cache row (-1: not stored) and position of every row, read
-    // once here so that no store below waits on a dependent global load.
-    int* rtab = reinterpret_cast<int*>(Cs + 4 * BM * LDC);
-    int* ptab = rtab + BM;
-    const bool is_v = n0 >= p.kv_d;
-    const int HD = p.hd, HALF = HD >> 1;
-    if (tid < BM) {
-      const int row = m0 + tid;
-      const int dr = row < p.M ? p.plan_row[row] : -1;
-      rtab[tid] = dr;
-      ptab[tid] = dr >= 0 ? p.plan_pos[row] : 0;
-    }
-    auto at = [&](int rr, int cc) { return Cs[((cc >> 5) * BM + rr) * LDC + (cc & 31)]; };
-    // K items (row, octet of eight rotated pairs): 8 octets per row of a slab, each stored
-    // as two 16-byte runs (dims i0..i0+7 and i0+hd/2..i0+hd/2+7 are contiguous in the key
-    // tile layout).  A thread's items are rows rr, rr + THREADS/8, ... of one octet, the
-    // same rows and dims in every slab, so their rotation-table entries are fetched once
-    // per tile, before the first slab (rows without a cache row fetch entry 0 and are
-    // skipped).  The barriers below order LDS traffic only, so the stores of one slab
-    // stay in flight while the next one is staged.
-    constexpr int KI = BM * 8 / THREADS;
-    static_assert(KI * THREADS == BM * 8, "whole items per thread");
-    const int oc = tid & 7;
-    const int kj = (8 * oc) / HALF;           // head inside the slab
-    const int i0 = 8 * oc - kj * HALF;
-    float4 cs[KI][4];
-    lds_barrier();                             // the row table
-    if (!is_v && p.rope_cs != nullptr) {
-#pragma unroll
-      for (int it = 0; it < KI; ++it) {
-        const float* c = p.rope_cs + (int64_t(ptab[(tid >> 3) + it * (THREADS / 8)]) * HALF + i0) * 2;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cs[it][q] = *reinterpret_cast<const float4*>(c + 4 * q);
-      }
-    }
-#pragma unroll 1
-    for (int slab = 0; slab < NB / 4; ++slab) {
-      if (slab > 0) lds_barrier();
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) {
-        const int b = wid * TN + tn;
-        if ((b >> 2) == slab) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int rr = 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-              Cs[((b & 3) * BM + rr) * LDC + (lane & 31)] = acc[i][tn][r];
-            }
-        }
-      }
-      lds_barrier();
-      const int c0 = n0 + 128 * slab - (is_v ? p.kv_d : 0);   // slab start inside K or V
-      if (c0 >= p.kv_d) continue;                             // columns past N
-      if (!is_v) {
-        const int j = kj;
-#pragma unroll
-        for (int it = 0; it < KI; ++it) {
-          const int rr = (tid >> 3) + it * (THREADS / 8);
-          const int drow = rtab[rr];
-          if (drow < 0) continue;
-          float y1[8], y2[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            y1[k] = at(rr, j * HD + i0 + k);
-            y2[k] = at(rr, j * HD + HALF + i0 + k);
-          }
-          if (p.rope_cs != nullptr) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              rope_rotate(y1[2 * q], y2[2 * q], cs[it][q].x, cs[it][q].y);
-              rope_rotate(y1[2 * q + 1], y2[2 * q + 1], cs[it][q].z, cs[it][q].w);
-            }
-          }
-          bf16_t* kh = static_cast<bf16_t*>(p.kc) + int64_t(c0 / HD + j) * p.cap * HD;
-          *reinterpret_cast<uint4*>(kh + kc_index(drow, i0, HD)) =
-              make_uint4(pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3]), pack_bf2(y1[4], y1[5]),
-                         pack_bf2(y1[6], y1[7]));
-          *reinterpret_cast<uint4*>(kh + kc_index(drow, i0 + HALF, HD)) =
-              make_uint4(pack_bf2(y2[0], y2[1]), pack_bf2(y2[2], y2[3]), pack_bf2(y2[4], y2[5]),
-                         pack_bf2(y2[6], y2[7]));
-        }
-      } else {
-        // Items (group of 8 rows, dim): consecutive threads on consecutive dims; a group
-        // whose 8 rows are 8 consecutive cache rows starting at a multiple of 8 is one
-        // 16-byte run of the value tile layout, any other group is stored element-wise.
-        for (int e = tid; e < (BM / 8) * 128; e += THREADS) {
-          const int cc = e & 127, rg = e >> 7;
-          const int row0 = m0 + 8 * rg;
-          if (row0 >= p.M) continue;
-          const int col = c0 + cc;
-          bf16_t* vh = static_cast<bf16_t*>(p.vtc) + int64_t(col / HD) * p.cap * HD;
-          const int i = col % HD;
-          const int d0 = rtab[8 * rg];
-          bool run = row0 + 8 <= p.M && d0 >= 0 && (d0 & 7) == 0;
-#pragma unroll
-          for (int k = 1; k < 8; ++k) run = run && rtab[8 * rg + k] == d0 + k;
-          if (run) {
-            float v[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = at(8 * rg + k, cc);
-            *reinterpret_cast<uint4*>(vh + vc_index(d0, i, HD)) =
-                make_uint4(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]),
-                           pack_bf2(v[6], v[7]));
-          } else {
-            for (int k = 0; k < 8 && row0 + k < p.M; ++k) {
-              const int dr = rtab[8 * rg + k];
-              if (dr >= 0) vh[vc_index(dr, i, HD)] = f2bf(at(8 * rg + k, cc));
-            }
-          }
-        }
-      }
     }
   } else {
     // Transposed tile: lane l holds row 32i + l%32 and, of 32-column block b, columns
@@ -638,37 +403,28 @@ static void launch_bf16_partial(const GemmArgs& a, int splits, hipStream_t s) {
                        a);
 }
 
-// One pass for 128 < M <= 256 rows: every row in one tile (192 or 256 rows), 8 waves of
-// one 32-column block, the weights streamed once (non-temporal).  Two 128-row tiles
-// re-streamed the weights through L2 instead (M = 192: 277 -> 211 us, M = 256: 289 -> 262
-// us).  One column block per wave reads a 1 KB activation fragment per MFMA, which at 256
-// rows is the LDS bandwidth of the CU.
-template <int BM>
+// One pass for 128 < M <= 192 rows: every row in one tile, 8 waves of one 32-column block,
+// the weights streamed once (non-temporal): 221 us for 129280 columns of 4096, against 227 to
+// 239 on the matrix-core bound tiles, which pad the rows to 256 and re-read the weights
+// through L2.  Above 192 rows those tiles are the faster ones (208 rows 239 against 266 us for
+// one tile of 256 rows, whose activation fragments are the LDS bandwidth of the CU).
 static void launch_bf16_argmax_tall(const GemmArgs& a, hipStream_t s) {
   constexpr int BN = 32 * 8;
   const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(8 * 64);
-  hipLaunchKernelGGL((gemm_kernel<bf16_t, BM, 8, 2, kEpiArgmax, 1, true>), grid, block, 0, s, a);
+  hipLaunchKernelGGL((gemm_kernel<bf16_t, 192, 8, 2, kEpiArgmax, 1, true>), grid, block, 0, s, a);
 }
 
-template <int NW, int TN, int STAGES>
+// Up to 128 rows: one row tile, every weight byte is read once, so the weights stream past the
+// caches.
 static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
-  if (a.M > 128 && a.M <= 192) return launch_bf16_argmax_tall<192>(a, s);
-  if (a.M > 192 && a.M <= 256) return launch_bf16_argmax_tall<256>(a, s);
-  const int BM = a.M <= 64 ? 64 : 128;
-  constexpr int BN = 32 * NW * TN;
-  const int mt = (a.M + BM - 1) / BM;
-  const int tiles = mt * ((a.N + BN - 1) / BN);
-  const dim3 grid(tiles, 1, 1), block(NW * 64);
-  // One row tile: every weight byte is read once, so the weights stream past the caches.
-  if (BM == 64)
+  constexpr int NW = 8, TN = 2, STAGES = 2, BN = 32 * NW * TN;
+  const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(NW * 64);
+  if (a.M <= 64)
     hipLaunchKernelGGL((gemm_kernel<bf16_t, 64, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
                        s, a);
-  else if (mt == 1)
+  else
     hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
                        s, a);
-  else
-    hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiArgmax, TN, (TN == 1), (TN == 2)>),
-                       grid, block, 0, s, a);
 }
 
 // fp32 tiles: 4 waves of one 32-column block and up to 128 rows, bound by the fp32 matrix
@@ -698,7 +454,7 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
                                   hipStream_t s) {
   if (bf16) {
     if (epi == kEpiPartial) {
-      if (plan.tn > 1) return launch_gemm_deep(a, plan, s);
+      if (plan.tn > 1) return launch_gemm_deep(kEpiPartial, a, plan, s);
       if (!plan.nt) {
         launch_bf16_partial<8, 1, 4, false>(a, plan.splits, s);
       } else if (plan.nw == 8) {
@@ -709,7 +465,11 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
         launch_bf16_partial<4, 1, 2>(a, plan.splits, s);
       }
     } else {
-      launch_bf16_argmax<8, 2, 2>(a, s);
+      if (a.M > 192) return launch_gemm_deep(kEpiArgmax, a, deep_argmax_plan(a.M), s);
+      if (a.M > 128)
+        launch_bf16_argmax_tall(a, s);
+      else
+        launch_bf16_argmax(a, s);
     }
     return hipGetLastError();
   }
@@ -831,6 +591,15 @@ hipError_t launch_gemm_partial2(const void* A, int64_t lda, const void* B, int M
   return launch_gemm_any(true, kEpiPartial, a, plan, s);
 }
 
+hipError_t launch_gemm_rows(const void* A, int64_t lda, const void* B, int M, int N, int K,
+                            GemmPlan plan, const float* bias, void* out, hipStream_t s) {
+  if (plan.tn < 2 || plan.splits != 1 || N % 4 != 0) return hipErrorInvalidValue;
+  GemmArgs a{};
+  a.A = A; a.lda = lda; a.B = B;
+  a.M = M; a.N = N; a.K = K; a.out = out; a.bias = bias;
+  return launch_gemm_deep(kEpiRows, a, plan, s);
+}
+
 hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int d, int hd,
                           GemmPlan plan, const int32_t* plan_pos, const int32_t* plan_row,
                           const float* rope_cs, void* kc, void* vtc, int64_t cap, hipStream_t s) {
@@ -843,18 +612,7 @@ hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int 
   a.M = M; a.N = 2 * d; a.K = d;
   a.plan_pos = plan_pos; a.plan_row = plan_row; a.rope_cs = rope_cs;
   a.kc = kc; a.vtc = vtc; a.cap = cap; a.kv_d = d; a.hd = hd;
-  const int tiles = ((M + 127) / 128) * ((2 * d + 511) / 512);
-  hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, 8, 2, kEpiKV, 2, false, true>), dim3(tiles), dim3(512),
-                     0, s, a);
-  return hipGetLastError();
-}
-
-GemmPlan lm_head_plan(int64_t) {
-  // 8 waves of two 32-column blocks each (512-column tiles).  Above 128 rows the product
-  // is matrix-core bound and two blocks per wave halve the LDS traffic per MFMA (M = 1024:
-  // 914 -> 848 us); at 128 rows and fewer it is a weight stream, and the wider tile halves
-  // the activation bytes each CU reads per weight byte (M = 128: 173 -> 166 us).
-  return GemmPlan{8, 1, 2};
+  return launch_gemm_deep(kEpiKV, a, plan, s);
 }
 
 hipError_t launch_lm_head_keys(bool bf16, const void* hidden, const void* W, int64_t M, int d,
@@ -871,7 +629,7 @@ hipError_t launch_lm_head_keys(bool bf16, const void* hidden, const void* W, int
     a.M = rows; a.N = V; a.K = d;
     a.C = logits != nullptr ? logits + r0 * V : nullptr;
     a.keys = keys + r0;
-    const hipError_t e = launch_gemm_any(bf16, kEpiArgmax, a, lm_head_plan(M), s);
+    const hipError_t e = launch_gemm_any(bf16, kEpiArgmax, a, GemmPlan{}, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

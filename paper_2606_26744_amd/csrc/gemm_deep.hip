@@ -21,7 +21,8 @@
 // Measured alone (random operands, warm): 16384 x 4096 -> 8192 972 -> 815 us with fp32 stores,
 // 16384 x 16384 -> 4096 1878 -> 1520 us, 1024 x 4096 -> 24576 in two K splits 204 -> 180 us,
 // 1024 x 12288 -> 4096 in four 96 -> 81 us (before: compiler-ordered loop of the 128 x 512
-// tiles).  Copies without stores run at 1.40-1.52 PFLOP/s, without any load from memory in
+// tiles).  With the other epilogues, same box: keys and values 838 us, bf16 rows 830, argmax
+// 779, fp32 rows 837.  Copies without stores run at 1.40-1.52 PFLOP/s, without any load from memory in
 // the loop at 1.60-1.72, the MFMAs alone at 1.67-1.80 (the power limit on such data).
 #include "common.hpp"
 #include "gemm_tile.hpp"
@@ -192,12 +193,280 @@ __device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const Bu
     if (u + j < nu) unit(u + j, j);
 }
 
+// ---------------------------------------------------------------------------- epilogues
+// Accumulator element r of block (i, t): product A.W^T: row 32i + 8(r/4) + 4(lane/32) + r%4,
+// column 32t + lane%32 of the wave; transposed product: row 32i + lane%32, column
+// 32t + 8(r/4) + 4(lane/32) + r%4.
+
+// fp32 C (or split-K partial) straight from the accumulators.
+template <int TM, int TN>
+__device__ __forceinline__ void store_partial(const f32x16_t (&acc)[TM][TN], const GemmArgs& p, int z,
+                                              int m0, int c0) {
+  const int lane = threadIdx.x & 63;
+  float* C = p.C + int64_t(z) * p.M * p.N;
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int col = c0 + 32 * t + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = m0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        if (row < p.M && col < p.N) C[int64_t(row) * p.N + col] = acc[i][t][r];
+      }
+  }
+}
+
+// Context K rows from the transposed product: a lane holds four consecutive dims of a row
+// and, in another of its blocks, the four dims half a head on, so RoPE needs no exchange; four
+// dims are 8 bytes of the key tile and the 64 lanes' runs are two pieces of 256 bytes.
+// rows[]: cache row (-1: not stored) of the tile's rows; tab: the rotation table's rows of
+// the tile, both in LDS.  16384 rows x 4096 in the cold step of 8 x 2048: 1010 -> 890 us for
+// the launch (before: two waves a SIMD in ping-pong, 128 columns at a time through LDS).
+constexpr int kRopeLd = 132;   // floats between the table rows in LDS
+
+__device__ __forceinline__ void store_keys(const f32x16_t (&acc)[4][4], const GemmArgs& p, int c0,
+                                           const int* rows, const float* tab) {
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int HD = p.hd, HALF = HD >> 1;
+  const bool wide = HD == 128;
+  const bool rope = p.rope_cs != nullptr;
+  // Block pair q: (0, 2), (1, 3) of one head of 128, or (0, 1), (2, 3) of two heads of 64.
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float* cs = tab + (32 * i + (lane & 31)) * kRopeLd + 8 * h;
+    const int drow = rows[32 * i + (lane & 31)];
+    const int rr = drow & 31;
+    const int64_t base = int64_t(drow >> 6) * 64 * HD +
+                         ((2 * ((drow & 63) >> 5) + ((rr >> 2) & 1)) * (HD >> 5) * 64 + 4 * (rr >> 3) + (rr & 3)) * 8 +
+                         4 * h;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      bf16_t* kh = static_cast<bf16_t*>(p.kc) + int64_t(wide ? c0 / 128 : c0 / 64 + q) * p.cap * HD + base;
+      const int slice = wide ? q : 0;   // 32-dim slice of the first half
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float y1[4], y2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const f32x16_t& a = wide ? acc[i][q] : acc[i][2 * q];
+          const f32x16_t& b = wide ? acc[i][2 + q] : acc[i][2 * q + 1];
+          y1[e] = a[4 * g + e];
+          y2[e] = b[4 * g + e];
+        }
+        if (rope) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float4 c = *reinterpret_cast<const float4*>(cs + ((wide ? 32 * q : 0) + 8 * g) * 2 + 4 * e);
+            rope_rotate(y1[2 * e], y2[2 * e], c.x, c.y);
+            rope_rotate(y1[2 * e + 1], y2[2 * e + 1], c.z, c.w);
+          }
+        }
+        if (drow >= 0) {
+          bf16_t* dst = kh + (slice * 64 + g * 16) * 8;
+          *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf2(y1[0], y1[1]), pack_bf2(y1[2], y1[3]));
+          *reinterpret_cast<uint2*>(dst + (HALF >> 5) * 512) =
+              make_uint2(pack_bf2(y2[0], y2[1]), pack_bf2(y2[2], y2[3]));
+        }
+      }
+    }
+  }
+}
+
+// Context V rows, from the transposed product too (one K loop for the kernel): a lane holds
+// four consecutive dims of a row; where a quad's four rows are four consecutive cache rows
+// that start at a multiple of 4, the quad turns its 4 x 4 values round (two exchanges of
+// packed pairs), so that each lane stores four rows of one dim, 8 bytes of the value tile;
+// single elements otherwise.
+__device__ __forceinline__ void store_values(const f32x16_t (&acc)[4][4], const GemmArgs& p, int c0,
+                                             const int* rows) {
+  const int lane = threadIdx.x & 63, h = lane >> 5, j = lane & 3;
+  const int HD = p.hd;
+  // Bytes of {partner, own} that give this lane (row j, row j^1) in row order of one dim of a pair.
+  const uint32_t sel = (j & 1) ? 0x03020706u : 0x05040100u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int4 d = *reinterpret_cast<const int4*>(rows + 32 * i + (lane & 28));
+    const bool run = d.x >= 0 && (d.x & 3) == 0 && d.y == d.x + 1 && d.z == d.x + 2 && d.w == d.x + 3;
+    const int own = j == 0 ? d.x : j == 1 ? d.y : j == 2 ? d.z : d.w;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int col = c0 + 32 * t;
+      bf16_t* vh = static_cast<bf16_t*>(p.vtc) + int64_t(col / HD) * p.cap * HD;
+      const int dim0 = col % HD + 4 * h;
+      const f32x16_t& a = acc[i][t];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const uint32_t lo = pack_bf2(a[4 * g], a[4 * g + 1]), hi = pack_bf2(a[4 * g + 2], a[4 * g + 3]);
+        // Even lanes then hold dims 0 and 2 of their and the next row, odd lanes 1 and 3 ...
+        const uint32_t y0 = __builtin_amdgcn_perm(__builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, true), lo, sel);
+        const uint32_t y1 = __builtin_amdgcn_perm(__builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, true), hi, sel);
+        // ... and lane j dim j of all four rows.
+        const uint32_t got = __builtin_amdgcn_mov_dpp(j < 2 ? y1 : y0, 0x4E, 0xF, 0xF, true);
+        const uint2 four = j < 2 ? make_uint2(y0, got) : make_uint2(got, y1);
+        const int dim = dim0 + 8 * g;
+        if (run) {
+          *reinterpret_cast<uint2*>(vh + vc_index(d.x, dim + j, HD)) = four;
+        } else if (own >= 0) {
+          vh[vc_index(own, dim, HD)] = bf16_t(lo);
+          vh[vc_index(own, dim + 1, HD)] = bf16_t(lo >> 16);
+          vh[vc_index(own, dim + 2, HD)] = bf16_t(hi);
+          vh[vc_index(own, dim + 3, HD)] = bf16_t(hi >> 16);
+        }
+      }
+    }
+  }
+}
+
+// Row maxima (lowest column on ties) of the transposed product: over a lane's registers,
+// across the lane halves by a shuffle, across the waves in LDS, one atomic per row into the
+// row's packed key.  The logits leave, when asked for, block by block through a region of LDS
+// of the wave's own.  129280 columns of 4096: 1024 rows 940 -> 826 us, 512 rows 493 -> 443, 300
+// rows 377 -> 338, 2048 rows 1837 -> 1613 (before: ping-pong tiles of 128 x 512).
+template <int TM, int TN>
+__device__ __forceinline__ void fold_argmax(const f32x16_t (&acc)[TM][TN], const GemmArgs& p, int m0,
+                                            int c0, float* lds) {
+  constexpr int BM = 32 * TM;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, h = lane >> 5, tok = lane & 31;
+  float best[TM];
+  int bcol[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    best[i] = -INFINITY;
+    bcol[i] = 0x7FFFFFFF;
+  }
+#pragma unroll
+  for (int t = 0; t < TN; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int col = c0 + 32 * t + 8 * (r >> 2) + 4 * h + (r & 3);
+      const bool in = col < p.N;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const float v = acc[i][t][r];
+        const bool take = in & (v > best[i]);
+        best[i] = take ? v : best[i];
+        bcol[i] = take ? col : bcol[i];
+      }
+    }
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const float ov = __shfl_xor(best[i], 32, kWave);
+    const int oc = __shfl_xor(bcol[i], 32, kWave);
+    if (ov > best[i] || (ov == best[i] && oc < bcol[i])) {
+      best[i] = ov;
+      bcol[i] = oc;
+    }
+  }
+  lds_barrier();   // the K loop's last reads
+  float* rv = lds;                                        // [wave][row] maxima
+  int* rc = reinterpret_cast<int*>(lds + 4 * BM);         // [wave][row] columns
+  if (lane < 32) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      rv[wid * BM + 32 * i + tok] = best[i];
+      rc[wid * BM + 32 * i + tok] = bcol[i];
+    }
+  }
+  lds_barrier();
+  for (int row = threadIdx.x; row < BM; row += kDeepThreads) {
+    float bv = rv[row];
+    int bc = rc[row];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const float ov = rv[w * BM + row];
+      const int oc = rc[w * BM + row];
+      if (ov > bv || (ov == bv && oc < bc)) {
+        bv = ov;
+        bc = oc;
+      }
+    }
+    if (m0 + row < p.M && bc != 0x7FFFFFFF) atomicMax(p.keys + m0 + row, argmax_key(bv, bc));
+  }
+  if (p.C == nullptr) return;
+  constexpr int LDC = 33;
+  float* own = lds + 8 * BM + wid * 32 * LDC;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) own[tok * LDC + 8 * (r >> 2) + 4 * h + (r & 3)] = acc[i][t][r];
+      __builtin_amdgcn_wave_barrier();
+      const int col = c0 + 32 * t + tok;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = m0 + 32 * i + 2 * r + h;
+        const float v = own[(2 * r + h) * LDC + tok];
+        if (row < p.M && col < p.N) p.C[int64_t(row) * p.N + col] = v;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// bf16 rows (+ bias per column, fp32) from the transposed product, 32 rows at a time through
+// a region of LDS of the wave's own, so that whole lines of a row leave together (stores
+// straight from the registers meet half lines: 16384 x 4096 -> 8192 883 us that way against
+// 837 for fp32 rows, 835 this way).
+template <int TM, int TN>
+__device__ __forceinline__ void store_rows(const f32x16_t (&acc)[TM][TN], const GemmArgs& p, int m0,
+                                           int c0, bf16_t* lds) {
+  constexpr int W = 32 * TN, LD = W + 8;        // columns of a wave, padded LDS row
+  constexpr int PER = W / 8, RPI = 64 / PER;    // 16-byte pieces of a row, rows a store
+  const int lane = threadIdx.x & 63, h = lane >> 5, tok = lane & 31;
+  bf16_t* own = lds + (threadIdx.x >> 6) * 32 * LD;
+  float* bias = reinterpret_cast<float*>(lds + 4 * 32 * LD);   // of the tile's columns
+  lds_barrier();   // the K loop's last reads
+  for (int c = threadIdx.x; c < 4 * W; c += kDeepThreads) {
+    const int col = c0 - (threadIdx.x >> 6) * W + c;
+    bias[c] = p.bias != nullptr && col < p.N ? p.bias[col] : -0.f;   // x + -0 is x
+  }
+  lds_barrier();
+  bias += (threadIdx.x >> 6) * W + 4 * h;
+  bf16_t* out = static_cast<bf16_t*>(p.out);
+  const bool whole = (p.N & 7) == 0;            // rows start on 16 bytes (else on 8)
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x16_t& a = acc[i][t];
+        const float4 b = *reinterpret_cast<const float4*>(bias + 32 * t + 8 * g);
+        *reinterpret_cast<uint2*>(own + tok * LD + 32 * t + 8 * g + 4 * h) =
+            make_uint2(pack_bf2(a[4 * g] + b.x, a[4 * g + 1] + b.y),
+                       pack_bf2(a[4 * g + 2] + b.z, a[4 * g + 3] + b.w));
+        HDF_PIN();
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 32 / RPI; ++q) {
+      const int r = q * RPI + lane / PER, c = (lane % PER) * 8;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(own + r * LD + c);
+      const int row = m0 + 32 * i + r, col = c0 + c;
+      if (row < p.M && col < p.N) {
+        bf16_t* dst = out + int64_t(row) * p.N + col;
+        if (whole) {
+          st16(dst, v);
+        } else {
+          *reinterpret_cast<uint2*>(dst) = make_uint2(v[0], v[1]);
+          if (col + 4 < p.N) *reinterpret_cast<uint2*>(dst + 4) = make_uint2(v[2], v[3]);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 template <int TM, int EPI>
 __global__ void __launch_bounds__(kDeepThreads, 1)
 gemm_deep_kernel(GemmArgs p) {
   using Tl = DeepTile<TM>;
   constexpr int TN = Tl::TN, BM = Tl::BM, BN = Tl::BN;
+  static_assert(EPI != kEpiKV || TM == 4, "whole heads a wave");
   __shared__ __attribute__((aligned(16))) unsigned char smem[Tl::kLds];
+  __shared__ __attribute__((aligned(16))) int row_tab[EPI == kEpiKV ? BM : 4];
+  __shared__ __attribute__((aligned(16))) float rope_tab[EPI == kEpiKV ? BM * kRopeLd : 4];
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -241,21 +510,42 @@ gemm_deep_kernel(GemmArgs p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
   bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-  if (k1 > k0)
-    deep_loop<TM, false>(acc, ra, p.lda, rb, (blk0 & 3) * 1024, k0 * 2, (k1 - k0) * 2, lds);
-
-  // fp32 C (or split-K partial z at C + z*M*N) straight from the accumulators.
-  float* C = p.C + int64_t(z) * p.M * p.N;
-#pragma unroll
-  for (int t = 0; t < TN; ++t) {
-    const int col = n0 + 32 * (wid * TN + t) + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row < p.M && col < p.N) C[int64_t(row) * p.N + col] = acc[i][t][r];
+  const int c0 = n0 + 32 * TN * wid;   // the wave's first column
+  if constexpr (EPI == kEpiKV) {
+    // Cache rows of the tile's rows and, for K, their rotation table rows, copied whole rows
+    // at a time (the epilogue's lanes reading them from memory would touch 32 rows a load)
+    // before the K loop, whose first loads they precede (copied after it: 9 us a tile).  Visible
+    // after the K loop's barriers.
+    if (threadIdx.x < BM) {
+      const int row = m0 + threadIdx.x;
+      row_tab[threadIdx.x] = row < p.M ? p.plan_row[row] : -1;
+    }
+    if (n0 < p.kv_d && p.rope_cs != nullptr) {
+      const int per = p.hd >> 2;   // 16-byte pieces of a table row
+#pragma unroll 8
+      for (int q = threadIdx.x; q < BM * per; q += kDeepThreads) {
+        const int r = q / per, c = q - r * per;
+        const int pos = max(p.plan_pos[min(m0 + r, p.M - 1)], 0);   // -1: a row that is not stored
+        *reinterpret_cast<u32x4*>(rope_tab + r * kRopeLd + 4 * c) =
+            ld16(p.rope_cs + int64_t(pos) * p.hd + 4 * c);
       }
+    }
+  }
+  constexpr bool SWAP = EPI != kEpiPartial;
+  if (k1 > k0)
+    deep_loop<TM, SWAP>(acc, ra, p.lda, rb, (blk0 & 3) * 1024, k0 * 2, (k1 - k0) * 2, lds);
+  if constexpr (EPI == kEpiKV) {
+    // d is a multiple of the tile's 512 columns, so a tile lies wholly in K or in V.
+    if (n0 < p.kv_d)
+      store_keys(acc, p, c0, row_tab, rope_tab);
+    else
+      store_values(acc, p, c0 - p.kv_d, row_tab);
+  } else if constexpr (EPI == kEpiArgmax) {
+    fold_argmax<TM, TN>(acc, p, m0, c0, reinterpret_cast<float*>(smem));
+  } else if constexpr (EPI == kEpiRows) {
+    store_rows<TM, TN>(acc, p, m0, c0, reinterpret_cast<bf16_t*>(smem));
+  } else {
+    store_partial<TM, TN>(acc, p, z, m0, c0);
   }
 }
 
@@ -269,11 +559,25 @@ static void launch_deep(const GemmArgs& a, int splits, hipStream_t s) {
   hipLaunchKernelGGL((gemm_deep_kernel<TM, EPI>), dim3(tiles, 1, splits), dim3(kDeepThreads), 0, s, a);
 }
 
-hipError_t launch_gemm_deep(const GemmArgs& a, const GemmPlan& plan, hipStream_t s) {
-  if (plan.tn == DeepTile<4>::TN)
+hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hipStream_t s) {
+  const bool wide = plan.tn == DeepTile<4>::TN;
+  if (epi == kEpiKV) {
+    launch_deep<4, kEpiKV>(a, 1, s);
+  } else if (epi == kEpiArgmax) {
+    if (wide)
+      launch_deep<4, kEpiArgmax>(a, 1, s);
+    else
+      launch_deep<8, kEpiArgmax>(a, 1, s);
+  } else if (epi == kEpiRows) {
+    if (wide)
+      launch_deep<4, kEpiRows>(a, 1, s);
+    else
+      launch_deep<8, kEpiRows>(a, 1, s);
+  } else if (wide) {
     launch_deep<4, kEpiPartial>(a, plan.splits, s);
-  else
+  } else {
     launch_deep<8, kEpiPartial>(a, plan.splits, s);
+  }
   return hipGetLastError();
 }
 
@@ -307,6 +611,13 @@ GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
     }
   }
   return GemmPlan{4, best_s, best_i == 0 ? DeepTile<8>::TN : DeepTile<4>::TN};
+}
+
+// The LM head's tile: 256 x 256, whose weights half as many row tiles re-read from HBM (8 to
+// 9% faster at equal rows), unless 128-row tiles pad the rows by that much less.
+GemmPlan deep_argmax_plan(int M) {
+  const int64_t pad256 = (int64_t(M) + 255) / 256 * 256, pad128 = (int64_t(M) + 127) / 128 * 128;
+  return GemmPlan{4, 1, pad128 * 109 < pad256 * 100 ? DeepTile<4>::TN : DeepTile<8>::TN};
 }
 
 }  // namespace hdf

@@ -37,10 +37,11 @@ hipError_t launch_accept_keys(unsigned long long* keys, int64_t M, int32_t* argm
                               const int32_t* target, int n_seq, int K, int32_t* acc,
                               int32_t* anchor, int32_t* offs, int32_t* toks, hipStream_t s);
 
-// ---------------------------------------------------------------- GEMM (gemm.hip)
+// ------------------------------------------- GEMM (gemm.hip, gemm_deep.hip)
 constexpr int kEpiPartial = 0;  // fp32 C / split-K partials
 constexpr int kEpiArgmax = 1;   // LM head: fused row argmax (+ optional fp32 logits in C)
 constexpr int kEpiKV = 2;       // context K/V rows: RoPE on K, stored into the cache layouts
+constexpr int kEpiRows = 3;     // bf16 rows (+ bias), one K split
 
 struct GemmArgs {
   const void* A;   // [M][lda] row-major activations
@@ -65,6 +66,9 @@ struct GemmArgs {
   void* vtc;              // [nh][hd][cap] value tiles of the layer
   int64_t cap;
   int kv_d, hd;
+  // kEpiRows: out[M][N] bf16 (16-byte aligned), N % 4 == 0; bias [N] fp32 or NULL.
+  void* out;
+  const float* bias;
 };
 
 int gemm_k_align(bool bf16);                       // K must be a multiple of this
@@ -81,9 +85,11 @@ GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K);
 // Two problems of the same K in one launch where the first one's row tiles (up to 256
 // rows) share weight columns: weights fetched through L2 (8 waves of one block).
 GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K);
-// Matrix-core bound bf16 problems (gemm_deep.hip): the plan, and fp32 partials by it.
+// Matrix-core bound bf16 problems (gemm_deep.hip): the plan, and the launch with epilogue
+// `epi` (kEpiPartial by the plan's splits, the others in one).
 GemmPlan deep_plan(int M, int N, int M2, int N2, int K);
-hipError_t launch_gemm_deep(const GemmArgs& a, const GemmPlan& plan, hipStream_t s);
+GemmPlan deep_argmax_plan(int M);
+hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hipStream_t s);
 size_t packed_weight_elems(int N, int K);          // rows rounded up to 128
 hipError_t launch_pack_weight(bool bf16, const void* src, void* dst, int N, int K, hipStream_t s);
 // C[z][M][N] (fp32) = A[M][K] . W[N][K]^T over the z-th of `splits` K ranges; W packed.
@@ -93,6 +99,10 @@ hipError_t launch_gemm_partial(bool bf16, const void* A, int64_t lda, const void
 hipError_t launch_gemm_partial2(const void* A, int64_t lda, const void* B, int M, int N,
                                 float* C, const void* A2, int64_t lda2, const void* B2, int M2,
                                 int N2, float* C2, int K, GemmPlan plan, hipStream_t s);
+// out[M][N] (bf16) = A . W^T (+ bias): for the matrix-core bound plans of one K split
+// (returns hipErrorInvalidValue otherwise).
+hipError_t launch_gemm_rows(const void* A, int64_t lda, const void* B, int M, int N, int K,
+                            GemmPlan plan, const float* bias, void* out, hipStream_t s);
 // Context K/V projection straight into the cache: A [M][d] normed context rows (bf16),
 // B the packed W_k; W_v rows (2d x d), RoPE on K at plan_pos, stores at plan_row.  Only
 // for plans of one K split and two-block waves and d % 512 == 0 (returns
@@ -107,8 +117,6 @@ hipError_t launch_lm_head(bool bf16, const void* hidden, const void* W, int64_t 
 // The GEMM of launch_lm_head only: the keys are left folded, not finalised or cleared.
 hipError_t launch_lm_head_keys(bool bf16, const void* hidden, const void* W, int64_t M, int d,
                                int V, unsigned long long* keys, float* logits, hipStream_t s);
-// Tile shape of the LM head's bf16 kernel for M rows (waves, blocks per wave).
-GemmPlan lm_head_plan(int64_t M);
 
 // ---------------------------------------------------------------- row-wise (rowwise.hip)
 struct QkvEpiArgs {

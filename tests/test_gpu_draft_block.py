@@ -310,3 +310,19 @@ def test_fp32_attention_tiles(hd, B, ctx, new, paged):
     wl.drafter = synth.DrafterShape(d=256, n_layers=1, n_heads=256 // hd, head_dim=hd, d_ff=512,
                                     vocab=500)
     _compare(DraftCase(wl, ctx, new, B=B, sub=31, paged=paged, spare_pages=3 if paged else 0))
+
+
+@pytest.mark.parametrize("hd,ctx,new,rope", [(128, [700, 1025, 64, 331], [700, 1001, 64, 331], True),
+                                             (64, [513, 1600, 3], [510, 1600, 3], True),
+                                             (128, [2049], [2049], False)])
+def test_cold_rows_stored_by_the_projection(hd, ctx, new, rope):
+    """Context rows projected alone (more than 2048 with the drafter's d, or ragged ones):
+    keys and values stored from the product's registers, with rows that start anywhere in a
+    cache tile, ends of sequences inside a row tile, both head sizes, and no RoPE."""
+    wl = synth.small_bf16()
+    wl.drafter = synth.DrafterShape(d=1024, n_layers=1, n_heads=1024 // hd, head_dim=hd, d_ff=1024,
+                                    vocab=500)
+    ctx, new = ctx * 2, new * 2          # more than 2048 new rows
+    assert sum(new) > 2048
+    _compare(DraftCase(wl, ctx, new, sub=41, rope=rope))
+    _compare(DraftCase(wl, ctx, new, sub=42, rope=rope, paged=True, spare_pages=2))

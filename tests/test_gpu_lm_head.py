@@ -180,3 +180,16 @@ def test_fp32_tiles(M, d, V):
     """fp32 tiles at the edges of their row counts (32, 64, 128 and several) and columns."""
     hid, w = _inputs(M, d, V, "f32", M + V + 7)
     _check(hid, w, dtype="f32")
+
+
+@pytest.mark.parametrize("M,d,V", [(192, 512, 640), (193, 576, 1000), (257, 512, 513), (384, 704, 777),
+                                   (385, 640, 129), (640, 512, 257), (1025, 1024, 2049)])
+def test_matrix_core_tiles(M, d, V):
+    """Row and column edges of the matrix-core bound tiles (both shapes), logits included.
+    (The logits' spread is 0.02 sqrt(d): below a few hundred columns more than a fifth of the
+    rows have top-2 margins under the compared margin, whatever computes them.)"""
+    hid, w = _inputs(M, d, V, "bf16", M + V + 3)
+    _check(hid, w)
+    am, mx, _ = hdf.lm_head_argmax(hid, hdf.pack_weight(w))    # without logits: the same rows
+    am2, mx2, _ = hdf.lm_head_argmax(hid, hdf.pack_weight(w), want_logits=True)
+    assert torch.equal(am, am2) and torch.equal(mx, mx2)
