@@ -416,8 +416,9 @@ static void launch_bf16_argmax_tall(const GemmArgs& a, hipStream_t s) {
 
 // Up to 128 rows: one row tile, every weight byte is read once, so the weights stream past the
 // caches.
-static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
-  constexpr int NW = 8, TN = 2, STAGES = 2, BN = 32 * NW * TN;
+template <int NW, int TN, int STAGES>
+static void launch_bf16_argmax_stream(const GemmArgs& a, hipStream_t s) {
+  constexpr int BN = 32 * NW * TN;
   const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(NW * 64);
   if (a.M <= 64)
     hipLaunchKernelGGL((gemm_kernel<bf16_t, 64, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
@@ -427,27 +428,76 @@ static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
                        s, a);
 }
 
-// fp32 tiles: 4 waves of one 32-column block and up to 128 rows, bound by the fp32 matrix
-// rate from about 64 rows (a 32 x 16 weight block is 2 KB against 512 matrix-core cycles per
-// 32 rows) and by the weight stream below.  Rows are rounded up to 32, 64 or 128, so at most
-// half of a tile's products are padding; one row tile streams its weights past the caches.
-// 64 rows: projections of K = 1024-4096 44 -> 12.6 us (median of five shapes), the
-// 1024 x 32000 head 249 -> 53 us against 64 x 64 tiles on the vector units.
-static int f32_rows(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+// The narrowest tile that covers the vocabulary in one round of workgroups: 128, 256 or 512
+// columns.  Wider ones leave CUs without a stream (4096-wide states, 64 rows: 32000 columns
+// 88 us in 512-column tiles, 55 in 256, 42 in 128; 50000 columns 93, 62, 71; 64000 columns 98,
+// 77, 88), narrower ones take a second round and re-read the activations more often (100000
+// columns 121, 129, 142).  Ring depths as measured at each width.
+static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
+  const int ncu = device_cu_count();
+  if ((int64_t(a.N) + 127) / 128 <= ncu) {
+    if (a.M <= 64)
+      launch_bf16_argmax_stream<4, 1, 4>(a, s);
+    else
+      launch_bf16_argmax_stream<4, 1, 2>(a, s);
+  } else if ((int64_t(a.N) + 255) / 256 <= ncu) {
+    launch_bf16_argmax_stream<8, 1, 2>(a, s);
+  } else {
+    launch_bf16_argmax_stream<8, 2, 2>(a, s);
+  }
+}
 
-template <int EPI>
+// fp32 tiles: 4 waves of one 32-column block and 32, 64 or 128 rows (the plan's tn row
+// blocks), bound by the fp32 matrix rate from about 64 rows (a 32 x 16 weight block is 2 KB
+// against 512 matrix-core cycles per 32 rows) and by the weight stream below.  One row tile
+// streams its weights past the caches.  64 rows: projections of K = 1024-4096 44 -> 12.6 us
+// (median of five shapes), the 1024 x 32000 head 249 -> 53 us against 64 x 64 tiles on the
+// vector units.
+template <int EPI, int BM, int STAGES>
 static void launch_f32(const GemmArgs& a, int splits, hipStream_t s) {
-  const int BM = f32_rows(a.M);
   const int mt = (a.M + BM - 1) / BM;
   const dim3 grid(mt * ((a.N + 127) / 128), 1, splits), block(256);
-  if (BM == 32)
-    hipLaunchKernelGGL((gemm_kernel<float, 32, 4, 4, EPI, 1, true>), grid, block, 0, s, a);
-  else if (BM == 64)
-    hipLaunchKernelGGL((gemm_kernel<float, 64, 4, 3, EPI, 1, true>), grid, block, 0, s, a);
-  else if (mt == 1)
-    hipLaunchKernelGGL((gemm_kernel<float, 128, 4, 2, EPI, 1, true>), grid, block, 0, s, a);
+  if (mt == 1)
+    hipLaunchKernelGGL((gemm_kernel<float, BM, 4, STAGES, EPI, 1, true>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((gemm_kernel<float, 128, 4, 2, EPI, 1, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((gemm_kernel<float, BM, 4, STAGES, EPI, 1, false>), grid, block, 0, s, a);
+}
+
+template <int EPI>
+static void launch_f32(const GemmArgs& a, const GemmPlan& plan, hipStream_t s) {
+  if (plan.tn == 1)
+    launch_f32<EPI, 32, 4>(a, plan.splits, s);
+  else if (plan.tn == 2)
+    launch_f32<EPI, 64, 3>(a, plan.splits, s);
+  else
+    launch_f32<EPI, 128, 2>(a, plan.splits, s);
+}
+
+// Rows of a tile and K splits of an fp32 problem.  A workgroup's products take 32 cycles per
+// 32 rows and unit of K on each SIMD (the fp32 matrix rate); tiles of 32 rows run 7% and tiles
+// of 128 rows 3% off the 64-row ones' pace at equal rows (128 rows x 1024 -> 32000: 77, 72 and
+// 78 us), so the smaller tile wins where it pads fewer rows (65 rows: 59, 72, 78) or gives idle
+// CUs a workgroup (64 rows -> 4000: 24 against 40 us).  Every split writes and the next kernel
+// reads an fp32 partial (about 1700 B a cycle over the chip); a split keeps two K steps.
+static GemmPlan f32_plan(int M, int N, int K, int max_splits) {
+  const int ncu = device_cu_count();
+  const int steps = (K + kBKf32 - 1) / kBKf32;
+  GemmPlan best{4, 1, 1};
+  double best_t = 1e30;
+  for (int tn : {2, 1, 4}) {
+    const int BM = 32 * tn;
+    const int64_t tiles = ((int64_t(M) + BM - 1) / BM) * ((N + 127) / 128);
+    const double pace = tn == 1 ? 1.07 : tn == 2 ? 1.0 : 1.03;
+    for (int sp = 1; sp <= max_splits && (sp == 1 || steps / sp >= 2); ++sp) {
+      const double mma = double((tiles * sp + ncu - 1) / ncu) * ((steps + sp - 1) / sp) * BM * kBKf32 * pace;
+      const double t = mma + (max_splits > 1 ? double(sp) * M * N * 8.0 / 1700.0 : 0.0);
+      if (t < best_t * (1.0 - 1e-9)) {
+        best_t = t;
+        best = GemmPlan{4, sp, tn};
+      }
+    }
+  }
+  return best;
 }
 
 static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPlan plan,
@@ -474,9 +524,9 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
     return hipGetLastError();
   }
   if (epi == kEpiPartial)
-    launch_f32<kEpiPartial>(a, plan.splits, s);
+    launch_f32<kEpiPartial>(a, plan, s);
   else
-    launch_f32<kEpiArgmax>(a, 1, s);
+    launch_f32<kEpiArgmax>(a, f32_plan(a.M, a.N, a.K, 1), s);
   return hipGetLastError();
 }
 
@@ -489,26 +539,7 @@ static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int nc
 
 GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
   const int ncu = device_cu_count();
-  if (!bf16) {
-    // A workgroup's products take 32 cycles per 32 rows and unit of K on each SIMD (the fp32
-    // matrix rate), its CU one workgroup at a time; every split writes and the next kernel
-    // reads an fp32 partial (about 1700 B a cycle over the chip).  The split with the least
-    // sum of the two, with at least two K steps each.
-    const int BM = f32_rows(M);
-    const int tiles = ((M + BM - 1) / BM) * ((N + 127) / 128);
-    const int steps = (K + kBKf32 - 1) / kBKf32;
-    int best_s = 1;
-    double best_t = 1e30;
-    for (int sp = 1; sp <= 16 && (sp == 1 || steps / sp >= 2); ++sp) {
-      const double mma = double((int64_t(tiles) * sp + ncu - 1) / ncu) * ((steps + sp - 1) / sp) * BM * kBKf32;
-      const double t = mma + double(sp) * M * N * 8.0 / 1700.0;
-      if (t < best_t - 1e-9) {
-        best_t = t;
-        best_s = sp;
-      }
-    }
-    return GemmPlan{4, best_s};
-  }
+  if (!bf16) return f32_plan(M, N, K, 16);
   const int nk = K / kBK;
   // One workgroup per CU works best for these weight streams: a CU holding two
   // workgroups while others hold one doubles the kernel's critical path.  Pick the

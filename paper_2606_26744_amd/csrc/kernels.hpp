@@ -76,7 +76,8 @@ int gemm_k_align(bool bf16);                       // K must be a multiple of th
 // 4, 6 or 8) and the number of K splits.
 struct GemmPlan {
   int nw, splits;
-  int tn = 1;       // 32-column blocks per wave (2 or 4: the tiles of gemm_deep.hip)
+  int tn = 1;       // bf16: 32-column blocks per wave (2 or 4: the tiles of gemm_deep.hip);
+                    // fp32: 32-row blocks of a tile
   bool nt = true;   // one-block waves: weights streamed past the caches
 };
 GemmPlan gemm_plan(bool bf16, int M, int N, int K);

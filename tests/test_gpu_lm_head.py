@@ -193,3 +193,11 @@ def test_matrix_core_tiles(M, d, V):
     am, mx, _ = hdf.lm_head_argmax(hid, hdf.pack_weight(w))    # without logits: the same rows
     am2, mx2, _ = hdf.lm_head_argmax(hid, hdf.pack_weight(w), want_logits=True)
     assert torch.equal(am, am2) and torch.equal(mx, mx2)
+
+
+@pytest.mark.parametrize("M,V", [(64, 32768), (65, 32769), (128, 65537), (5, 65536), (128, 12801)])
+def test_stream_tile_widths(M, V):
+    """Vocabularies at which the tile of up to 128 rows changes its width (one round of
+    workgroups: 256 tiles of 128, then of 256 columns), and a ragged last group."""
+    hid, w = _inputs(M, 512, V, "bf16", M + V)
+    _check(hid, w)
