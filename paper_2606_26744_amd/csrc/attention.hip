@@ -89,7 +89,7 @@ constexpr int kAttnThreads = 64 * kAttnWaves;
 // after its scores (the keys alone fill half of the registers), and P needs no split.
 // Bound by the fp32 matrix rate (a 64-key tile of a wave is 64*HD MFMA passes against 512*HD
 // bytes).  One thread per query over all keys in turn took 1945 us a layer at 4 sequences x
-// 512 positions x 16 heads of 64; the whole two-layer step went from 4961 to 993 us.
+// 512 positions x 16 heads of 64; now 17 us (21.6 with the value loads left to the compiler).
 template <typename T, int HD, bool FUSE>
 __global__ void __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)))
 attn_kernel(AttnArgs a, T* __restrict__ out) {
@@ -261,8 +261,21 @@ attn_kernel(AttnArgs a, T* __restrict__ out) {
     if constexpr (!F32) load_v(i);
     const int nval = valid_of(i);
     float sv[4][4];
+    F32x8 vv[F32 ? 2 : 1][NDT];   // fp32: V^T operands of the two 32-key steps
+    const T* vt = v_src(i);
+    auto load_vv = [&](int ks) {
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) vv[F32 ? ks : 0][dt] = ld_nt32(reinterpret_cast<const float*>(vt) + (ks * NDT + dt) * 512);
+      __builtin_amdgcn_sched_barrier(0);
+    };
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
+      // Half of the keys' registers are free: the first step's values follow here, so that
+      // their latency runs beside the other half's products and the softmax (left to the
+      // compiler each value load sat next to its use, a memory round trip apiece).
+      if constexpr (F32) {
+        if (st == 2) load_vv(0);
+      }
       f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
@@ -303,9 +316,9 @@ attn_kernel(AttnArgs a, T* __restrict__ out) {
       for (int e = 0; e < 4; ++e) oacc[dt][e] *= alpha;
 
     if constexpr (F32) {
-      // V^T operands as they come, eight keys of a dim a lane; a partial tile's keys past
-      // the valid ones are zeroed (see below).
-      const T* vt = v_src(i);
+      // V^T operands, eight keys of a dim a lane; a partial tile's keys past the valid ones are
+      // zeroed (see below).
+      load_vv(1);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         F32x8 pf;
@@ -314,7 +327,7 @@ attn_kernel(AttnArgs a, T* __restrict__ out) {
         const int nvalid = nval - (32 * ks + 8 * g);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-          F32x8 vop = ld_nt32(vt + (ks * NDT + dt) * 512);
+          F32x8 vop = vv[ks][dt];
           if (nval < kKeyTile) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) vop.v[e >> 2][e & 3] = e < nvalid ? vop.v[e >> 2][e & 3] : 0u;
