@@ -139,21 +139,35 @@ def _check(st: int):
         raise HdfError(st, lib().hdf_last_error().decode())
 
 
+# The calls below run once per kernel launch, and a small launch is over in about 5 us: the
+# marshalling passes plain integers (the declared argument types convert them) and reads the
+# current stream's handle without building a stream object.
+
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return _current_raw_stream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _raw_stream_of(device: int) -> int:
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# torch's own accessor of the raw handle where this build has it.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream_of)
+
+_DTYPES = {torch.bfloat16: HDF_BF16, torch.float32: HDF_F32}
 
 
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return HDF_BF16
-    if t.dtype == torch.float32:
-        return HDF_F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    d = _DTYPES.get(t.dtype)
+    if d is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return d
 
 
 def _dev(*ts):
