@@ -38,6 +38,7 @@
 namespace hdf {
 
 constexpr int kBK = 64;        // K granularity of the bf16 tiles (K % kBK == 0)
+constexpr int kShortSteps = 32;   // K steps up to which the stream plan weighs steps against partials
 constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last half step is zero-filled)
 
 // TN: 32-column weight blocks per wave (1, 2 or 4).  Each activation fragment read from
@@ -505,7 +506,9 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
   if (bf16) {
     if (epi == kEpiPartial) {
       if (plan.tn > 1) return launch_gemm_deep(kEpiPartial, a, plan, s);
-      if (!plan.nt) {
+      if (!plan.nt && plan.nw == 4) {
+        launch_bf16_partial<4, 1, 4, false>(a, plan.splits, s);
+      } else if (!plan.nt) {
         launch_bf16_partial<8, 1, 4, false>(a, plan.splits, s);
       } else if (plan.nw == 8) {
         launch_bf16_partial<8, 1>(a, plan.splits, s);
@@ -556,7 +559,9 @@ GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
 GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K) {
   // The row tiles of the first problem (at most two) read the same weight columns at
   // about the same time on one XCD: 8-wave tiles with the weights fetched through L2.
-  GemmPlan p = plan_stream(128, M, N, M2, N2, K / kBK, device_cu_count(), {8});
+  // (4 waves for narrow problems, whose 8-wave tiles are few: 64 + 64 rows x 1024 -> 3072 48
+  // workgroups in place of 24, the two-layer step 150.9 -> 147.3 us.)
+  GemmPlan p = plan_stream(128, M, N, M2, N2, K / kBK, device_cu_count(), {4, 8});
   p.nt = false;
   return p;
 }
@@ -564,6 +569,26 @@ GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K) {
 static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int ncu,
                             std::initializer_list<int> waves) {
   const int tn = 1;
+  if (nk <= kShortSteps) {
+    // Short K: the launch is a chain of K steps (0.22 us each at 64 rows, 0.35 at 128) and the
+    // partials that each split adds (3.8 TB/s written and read back); the narrowest tiles and
+    // the split with the least sum, in one round and with three steps at least.
+    const int tiles = ((M + BM - 1) / BM) * ((N + 127) / 128) + ((M2 + BM - 1) / BM) * ((N2 + 127) / 128);
+    if (tiles <= ncu) {
+      const double step = BM == 64 ? 0.22 : 0.35;
+      const double part = (double(M) * N + double(M2) * N2) * 8.0 / 3.8e6;
+      int best_s = 1;
+      double best_t = 1e30;
+      for (int s = 1; s <= 16 && tiles * s <= ncu && (s == 1 || nk / s >= 3); ++s) {
+        const double t = step * ((nk + s - 1) / s) + part * s;
+        if (t < best_t) {
+          best_t = t;
+          best_s = s;
+        }
+      }
+      return GemmPlan{4, best_s, tn};
+    }
+  }
   GemmPlan best{4, 1, tn};
   double best_fill = -1.0;
   for (int nw : waves) {
