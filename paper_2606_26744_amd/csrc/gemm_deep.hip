@@ -1,13 +1,15 @@
 // The matrix-core bound tiles (bf16, more than 128 rows): C = A . W^T over the packed weight
-// layout described in gemm.hip, 4 waves of 16 blocks of 32 x 32, one wave per SIMD.  Two tile
-// shapes of the same area:
-//   TM = 4: 128 rows x 512 columns, a wave owns all rows and one 128-row weight group;
-//   TM = 8: 256 rows x 256 columns, a wave owns all rows and half a weight group.
+// layout described in gemm.hip, 4 waves of TM x TN blocks of 32 x 32, one wave per SIMD, each
+// with all rows of the tile:
+//   TM = 4, TN = 4: 128 rows x 512 columns, a wave owns one 128-row weight group;
+//   TM = 8, TN = 2: 256 rows x 256 columns, a wave owns half a weight group;
+//   TM = 4, TN = 2: 128 rows x 256 columns, half the area at 1.18 times its share of the time,
+//     for problems that do not fill whole rounds of the large tiles.
 //
-// K loop.  A unit is 32 of K, two sub-steps of 16 MFMAs, which keep the matrix core of a
-// SIMD busy for 1024 cycles; the sixteen accumulators fill the accumulation registers.
-//   Weights: 32 KB (TM = 4) or 16 KB (TM = 8) a unit and workgroup straight into a register
-//     ring of R units, issued R - 1 units before their use.
+// K loop.  A unit is 32 of K, two sub-steps of 16 (8) MFMAs, which keep the matrix core of a
+// SIMD busy for 1024 (512) cycles; sixteen accumulators fill the accumulation registers.
+//   Weights: 8 KB a unit and block of TN, straight into a register ring of R units, issued
+//     R - 1 units before their use.
 //   Activations: loaded two units (64 of K, whole 128-byte lines) at a time, stored into
 //     swizzled LDS unit buffers CU units before their use; one workgroup barrier per CU units.
 //     A wave reads the fragments of a sub-step during the sub-step before it.
@@ -55,9 +57,9 @@ __device__ __forceinline__ u32x4 buf_ld16(BufRsrc r, int lane_off, int uniform_o
 // one chunk each) meet distinct banks.
 __device__ __forceinline__ int unit_swizzle(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
-template <int TM>
+template <int TM_, int TN_>
 struct DeepTile {
-  static constexpr int TN = 16 / TM;
+  static constexpr int TM = TM_, TN = TN_;
   static constexpr int BM = 32 * TM, BN = 128 * TN;
   static constexpr int UK = 32;
   static constexpr int CU = TM == 4 ? 4 : 2;            // units per barrier
@@ -69,17 +71,19 @@ struct DeepTile {
 };
 
 // acc[i][t] += rows 32i.. of the tile x columns of the wave's block t, over units ku0 ..
-// ku0 + nu - 1 (nu even, at least 2).  SWAP: the transposed product (the weights as the A
-// operand).  On return every wave has left the loop's last LDS read behind, not a barrier.
-template <int TM, bool SWAP>
-__device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const BufRsrc ra_, int64_t lda,
-                                          const BufRsrc rb_, int blk_off, int ku0, int nu,
-                                          bf16_t* lds) {
-  using Tl = DeepTile<TM>;
-  constexpr int TN = Tl::TN, UK = Tl::UK, CU = Tl::CU, NB = Tl::NB, UB = Tl::UB, PCH = Tl::PCH;
+// ku0 + nu - 1 (nu even, at least 2).  The first half of the blocks lies from byte off0 of
+// every 16 K of rb0 on, the second from off1 of rb1.  SWAP: the transposed product (the weights
+// as the A operand).  On return every wave has left the loop's last LDS read behind, not a
+// barrier.
+template <int TM, int TN, bool SWAP>
+__device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][TN], const BufRsrc ra_, int64_t lda,
+                                          const BufRsrc rb0, int off0, const BufRsrc rb1, int off1,
+                                          int ku0, int nu, bf16_t* lds) {
+  using Tl = DeepTile<TM, TN>;
+  constexpr int UK = Tl::UK, CU = Tl::CU, NB = Tl::NB, UB = Tl::UB, PCH = Tl::PCH;
   constexpr int R = kDeepRing, D = R - 1, AH = PCH / 2;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int bv = lane * 16 + blk_off;
+  const int bv0 = lane * 16 + off0, bv1 = lane * 16 + off1;
   int av[PCH], al[PCH];   // chunk q of a pair: row q/8, 16-byte column q%8 (unit q%8/4)
 #pragma unroll
   for (int j = 0; j < PCH; ++j) {
@@ -100,7 +104,8 @@ __device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const Bu
     dst[j] = buf_ld16(ra_, av[j], (ku0 / 2 + min(pr, np - 1)) * 128);
   };
   auto b_load = [&](int u, int ss, int t, u32x4 (*dst)[TN]) {
-    dst[ss][t] = buf_ld16(rb_, bv + t * 1024, (ku0 + u) * 8192 + ss * 4096);
+    const int at = (ku0 + u) * 8192 + ss * 4096;
+    dst[ss][t] = t < TN / 2 ? buf_ld16(rb0, bv0 + t * 1024, at) : buf_ld16(rb1, bv1 + (t - TN / 2) * 1024, at);
   };
   auto a_store = [&](const u32x4* src, int j, int buf) {
     *reinterpret_cast<u32x4*>(&lds[buf * UB + al[j]]) = src[j];
@@ -150,13 +155,19 @@ __device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const Bu
     auto st = [&](int x) { a_store(ra[rs], h + x, wbuf); HDF_PIN(); };
     auto la = [&](int x) { a_load((u >> 1) + CU / 2 + 1, h + x, ra[rs ^ 1]); HDF_PIN(); };
     auto lb = [&](int ss, int t) { b_load(u + D, ss, t, rb[(s + D) % R]); HDF_PIN(); };
+    constexpr int NM = TM * TN;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      if constexpr (TM == 4) {
+    for (int k = 0; k < NM; ++k) {
+      if constexpr (TM == 4 && TN == 4) {
         if (k < 8 && k % 2 == 0) rd1(k / 2);
         if (k < 12 && k % 3 == 1) lb(0, k / 3);
         if (k == 9 || k == 11) st((k - 9) / 2);
         if (k == 13 || k == 15) la((k - 13) / 2);
+      } else if constexpr (TM == 4) {
+        if (k < 4) rd1(k);
+        if (k == 1 || k == 5) lb(0, k / 4);
+        if (k == 4 || k == 6) st((k - 4) / 2);
+        if (k == 5 || k == 7) la((k - 5) / 2);
       } else {
         if (k % 2 == 0) rd1(k / 2);
         if (k % 4 == 1) st(k / 4);
@@ -171,10 +182,13 @@ __device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][16 / TM], const Bu
       HDF_PIN();
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      if constexpr (TM == 4) {
+    for (int k = 0; k < NM; ++k) {
+      if constexpr (TM == 4 && TN == 4) {
         if (k < 8 && k % 2 == 0) rd0(k / 2);
         if (k % 4 == 3) lb(1, k / 4);
+      } else if constexpr (TM == 4) {
+        if (k < 4) rd0(k);
+        if (k == 4 || k == 6) lb(1, (k - 4) / 2);
       } else {
         if (k % 2 == 0) rd0(k / 2);
         if (k == 5 || k == 11) lb(1, (k - 5) / 6);
@@ -458,12 +472,12 @@ __device__ __forceinline__ void store_rows(const f32x16_t (&acc)[TM][TN], const 
   }
 }
 
-template <int TM, int EPI>
+template <int TM, int TN, int EPI>
 __global__ void __launch_bounds__(kDeepThreads, 1)
 gemm_deep_kernel(GemmArgs p) {
-  using Tl = DeepTile<TM>;
-  constexpr int TN = Tl::TN, BM = Tl::BM, BN = Tl::BN;
-  static_assert(EPI != kEpiKV || TM == 4, "whole heads a wave");
+  using Tl = DeepTile<TM, TN>;
+  constexpr int BM = Tl::BM, BN = Tl::BN;
+  static_assert(EPI != kEpiKV || (TM == 4 && TN == 4), "whole heads a wave");
   __shared__ __attribute__((aligned(16))) unsigned char smem[Tl::kLds];
   __shared__ __attribute__((aligned(16))) int row_tab[EPI == kEpiKV ? BM : 4];
   __shared__ __attribute__((aligned(16))) float rope_tab[EPI == kEpiKV ? BM * kRopeLd : 4];
@@ -502,6 +516,7 @@ gemm_deep_kernel(GemmArgs p) {
   const bf16_t* B = static_cast<const bf16_t*>(p.B) + int64_t(grp) * (p.K >> 4) * 2048;
   const BufRsrc ra = buf_rsrc(A, int((int64_t(min(BM, p.M - m0) - 1) * p.lda + p.K) * 2));
   const BufRsrc rb = buf_rsrc(B, k1 * 2 * 8192);
+  const int off = (blk0 & 3) * 1024;
   f32x16_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -533,7 +548,7 @@ gemm_deep_kernel(GemmArgs p) {
   }
   constexpr bool SWAP = EPI != kEpiPartial;
   if (k1 > k0)
-    deep_loop<TM, SWAP>(acc, ra, p.lda, rb, (blk0 & 3) * 1024, k0 * 2, (k1 - k0) * 2, lds);
+    deep_loop<TM, TN, SWAP>(acc, ra, p.lda, rb, off, rb, off + TN / 2 * 1024, k0 * 2, (k1 - k0) * 2, lds);
   if constexpr (EPI == kEpiKV) {
     // d is a multiple of the tile's 512 columns, so a tile lies wholly in K or in V.
     if (n0 < p.kv_d)
@@ -551,73 +566,83 @@ gemm_deep_kernel(GemmArgs p) {
 
 // ---------------------------------------------------------------------------- host side
 
-template <int TM, int EPI>
+template <int TM, int TN, int EPI>
 static void launch_deep(const GemmArgs& a, int splits, hipStream_t s) {
-  using Tl = DeepTile<TM>;
+  using Tl = DeepTile<TM, TN>;
   const int tiles = ((a.M + Tl::BM - 1) / Tl::BM) * ((a.N + Tl::BN - 1) / Tl::BN) +
                     ((a.M2 + Tl::BM - 1) / Tl::BM) * ((a.N2 + Tl::BN - 1) / Tl::BN);
-  hipLaunchKernelGGL((gemm_deep_kernel<TM, EPI>), dim3(tiles, 1, splits), dim3(kDeepThreads), 0, s, a);
+  hipLaunchKernelGGL((gemm_deep_kernel<TM, TN, EPI>), dim3(tiles, 1, splits), dim3(kDeepThreads), 0, s, a);
+}
+
+template <int EPI>
+static void launch_tile(const GemmArgs& a, const GemmPlan& plan, int splits, hipStream_t s) {
+  if (plan.bm == 256)
+    launch_deep<8, 2, EPI>(a, splits, s);
+  else if (plan.tn == 4)
+    launch_deep<4, 4, EPI>(a, splits, s);
+  else
+    launch_deep<4, 2, EPI>(a, splits, s);
 }
 
 hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hipStream_t s) {
-  const bool wide = plan.tn == DeepTile<4>::TN;
-  if (epi == kEpiKV) {
-    launch_deep<4, kEpiKV>(a, 1, s);
-  } else if (epi == kEpiArgmax) {
-    if (wide)
-      launch_deep<4, kEpiArgmax>(a, 1, s);
-    else
-      launch_deep<8, kEpiArgmax>(a, 1, s);
-  } else if (epi == kEpiRows) {
-    if (wide)
-      launch_deep<4, kEpiRows>(a, 1, s);
-    else
-      launch_deep<8, kEpiRows>(a, 1, s);
-  } else if (wide) {
-    launch_deep<4, kEpiPartial>(a, plan.splits, s);
-  } else {
-    launch_deep<8, kEpiPartial>(a, plan.splits, s);
-  }
+  if (epi == kEpiKV)
+    launch_deep<4, 4, kEpiKV>(a, 1, s);
+  else if (epi == kEpiArgmax && plan.bm == 256)
+    launch_deep<8, 2, kEpiArgmax>(a, 1, s);
+  else if (epi == kEpiArgmax)
+    launch_deep<4, 4, kEpiArgmax>(a, 1, s);
+  else if (epi == kEpiRows)
+    launch_tile<kEpiRows>(a, plan, 1, s);
+  else
+    launch_tile<kEpiPartial>(a, plan, plan.splits, s);
   return hipGetLastError();
 }
 
-// The tile of the shape with fewer rounds of workgroups over the CUs, and the K split: the
-// time is about the number of rounds times the K range of one workgroup, plus the fp32
-// partials of every extra split (charged 15% each).  On ties the 256 x 256 tiles up to 2048
-// rows, where the weights come from HBM and half as many row tiles re-read them (1024 x 4096
-// -> 24576: 180 against 212 us; -> 129280 862 against 938; 1024 x 12288 -> 4096 82.5 against
-// 80.8), the 128 x 512 tiles above, whose fragments cost half the LDS reads (16384 x 4096 ->
-// 8192: 815 against 820 us, 16384 x 16384 -> 4096 1520 against 1553).
+// Tile shape and K split by the least estimated time: rounds of workgroups over the CUs, each
+// its units of K (0.72 us for the large tiles, 0.415 for 128 x 256) and 5 us of start and end,
+// plus the fp32 partials of every split, written here and read by the next kernel (5.2 TB/s).
+// 1024 rows, with that reader: 4096 -> 24576 206 us as 256 x 256 tiles in two splits, 196 as
+// 128 x 256 in one; 12288 -> 4096 83 in four splits, 80 in two (and half the partials);
+// 4096 -> 4096 38 and 32; 4096 -> 20480 171 as 256 x 256 in one, 142.  Of the large shapes, 256
+// x 256 up to 2048 rows, where the weights come from HBM and half as many row tiles re-read
+// them (1024 x 4096 -> 24576 in two splits: 180 against 212 us; -> 129280 862 against 938),
+// 128 x 512 above, whose fragments cost half the LDS reads (16384 x 4096 -> 8192: 815 against
+// 820 us, 16384 x 16384 -> 4096 1520 against 1553), unless the other one takes fewer rounds.
 GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
   const int ncu = device_cu_count();
   const int nk = K / 64;
-  auto tiles_of = [&](int bm, int bn) {
-    return int64_t((M + bm - 1) / bm) * ((N + bn - 1) / bn) + int64_t((M2 + bm - 1) / bm) * ((N2 + bn - 1) / bn);
-  };
-  const int64_t tiles[2] = {tiles_of(256, 256), tiles_of(128, 512)};
   const bool tall = M > 2048 || M2 > 2048;
-  int best_s = 1, best_i = 0;
+  struct Shape { int bm, tn; double unit; };
+  const Shape shapes[3] = {{tall ? 128 : 256, tall ? 4 : 2, 0.72}, {tall ? 256 : 128, tall ? 2 : 4, 0.73},
+                           {128, 2, 0.415}};
+  const double part = (double(M) * N + double(M2) * N2) * 8.0 / 5.2e6;
+  GemmPlan best{4, 1, 2};
+  best.bm = 256;
   double best_t = 1e30;
-  for (int sp = 1; sp <= 8; ++sp) {
-    if (sp > 1 && nk / sp < 8) break;
-    for (int x = 0; x < 2; ++x) {
-      const int i = tall ? 1 - x : x;
-      const double t = double((tiles[i] * sp + ncu - 1) / ncu) / sp * (1.0 + 0.15 * (sp - 1));
-      if (t < best_t - 1e-9) {
+  for (int sp = 1; sp <= 8 && (sp == 1 || nk / sp >= 8); ++sp)
+    for (const Shape& x : shapes) {
+      const int bn = 128 * x.tn;
+      const int64_t tiles = ((int64_t(M) + x.bm - 1) / x.bm) * ((N + bn - 1) / bn) +
+                            ((int64_t(M2) + x.bm - 1) / x.bm) * ((N2 + bn - 1) / bn);
+      const double rounds = double((tiles * sp + ncu - 1) / ncu);
+      const double t = rounds * (2.0 * ((nk + sp - 1) / sp) * x.unit + 5.0) + part * sp;
+      if (t < best_t) {
         best_t = t;
-        best_s = sp;
-        best_i = i;
+        best = GemmPlan{4, sp, x.tn};
+        best.bm = x.bm;
       }
     }
-  }
-  return GemmPlan{4, best_s, best_i == 0 ? DeepTile<8>::TN : DeepTile<4>::TN};
+  return best;
 }
 
 // The LM head's tile: 256 x 256, whose weights half as many row tiles re-read from HBM (8 to
 // 9% faster at equal rows), unless 128-row tiles pad the rows by that much less.
 GemmPlan deep_argmax_plan(int M) {
   const int64_t pad256 = (int64_t(M) + 255) / 256 * 256, pad128 = (int64_t(M) + 127) / 128 * 128;
-  return GemmPlan{4, 1, pad128 * 109 < pad256 * 100 ? DeepTile<4>::TN : DeepTile<8>::TN};
+  const bool low = pad128 * 109 < pad256 * 100;
+  GemmPlan p{4, 1, low ? 4 : 2};
+  p.bm = low ? 128 : 256;
+  return p;
 }
 
 }  // namespace hdf

@@ -79,6 +79,7 @@ struct GemmPlan {
   int tn = 1;       // bf16: 32-column blocks per wave (2 or 4: the tiles of gemm_deep.hip);
                     // fp32: 32-row blocks of a tile
   bool nt = true;   // one-block waves: weights streamed past the caches
+  int bm = 128;     // rows of a tile of gemm_deep.hip
 };
 GemmPlan gemm_plan(bool bf16, int M, int N, int K);
 // Plan of two problems of the same K launched together (M2 = 0: one problem).

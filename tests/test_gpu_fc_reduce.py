@@ -80,3 +80,9 @@ def test_matrix_core_tiles(n, m, d):
     """The matrix-core bound tiles around their row and column edges, both tile shapes, and K
     of one, three, five, seven and more 64-K steps (a part of the loop's unrolled units)."""
     _case(n, m, d, "bf16", n + m, n % 2 == 0)
+
+
+@pytest.mark.parametrize("n,m,d", [(1024, 4, 1280), (900, 2, 2304), (700, 4, 640), (513, 2, 1920)])
+def test_matrix_core_small_tiles(n, m, d):
+    """Shapes whose plan takes the 128 x 256 tiles, with and without K splits."""
+    _case(n, m, d, "bf16", n + m, n % 2 == 0)
