@@ -722,10 +722,14 @@ static hdf_status draft_block_impl(const hdf_drafter* w, int n_seq, int B, const
     HDF_TRY(hdf::launch_residual_norm(bf, parts, So, w->mlp_norm[l], w->eps, M, d, h, u, s));
 
     // act = SiLU(u Wg^T) * (u Wu^T); h += act Wd^T; next norm.
-    const hdf::GemmPlan Sgp = hdf::gemm_plan(bf, M, 2 * F, d);
-    const int Sg = Sgp.splits;
-    HDF_TRY(hdf::launch_gemm_partial(bf, u, d, w->w_gate_up[l], M, 2 * F, d, Sgp, parts, s));
-    HDF_TRY(hdf::launch_silu_epilogue(bf, parts, Sg, M, F, act, s));
+    hdf::GemmPlan Sgp;
+    if (bf && hdf::gemm_gated_plan(M, F, d, &Sgp)) {
+      HDF_TRY(hdf::launch_gemm_gated(u, d, w->w_gate_up[l], M, F, d, Sgp, act, s));
+    } else {
+      Sgp = hdf::gemm_plan(bf, M, 2 * F, d);
+      HDF_TRY(hdf::launch_gemm_partial(bf, u, d, w->w_gate_up[l], M, 2 * F, d, Sgp, parts, s));
+      HDF_TRY(hdf::launch_silu_epilogue(bf, parts, Sgp.splits, M, F, act, s));
+    }
     const hdf::GemmPlan Sdp = hdf::gemm_plan(bf, M, d, F);
     const int Sd = Sdp.splits;
     HDF_TRY(hdf::launch_gemm_partial(bf, act, F, w->w_down[l], M, d, F, Sdp, parts, s));

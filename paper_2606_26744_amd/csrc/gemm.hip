@@ -656,6 +656,19 @@ hipError_t launch_gemm_rows(const void* A, int64_t lda, const void* B, int M, in
   return launch_gemm_deep(kEpiRows, a, plan, s);
 }
 
+bool gemm_gated_plan(int M, int F, int K, GemmPlan* plan) {
+  return M > 128 && F % 64 == 0 && deep_gated_plan(M, F, K, plan);
+}
+
+hipError_t launch_gemm_gated(const void* A, int64_t lda, const void* W, int M, int F, int K,
+                             GemmPlan plan, void* act, hipStream_t s) {
+  if (plan.tn < 2 || plan.splits != 1 || F % 64 != 0) return hipErrorInvalidValue;
+  GemmArgs a{};
+  a.A = A; a.lda = lda; a.B = W;
+  a.M = M; a.N = 2 * F; a.K = K; a.out = act;
+  return launch_gemm_deep(kEpiGated, a, plan, s);
+}
+
 hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int d, int hd,
                           GemmPlan plan, const int32_t* plan_pos, const int32_t* plan_row,
                           const float* rope_cs, void* kc, void* vtc, int64_t cap, hipStream_t s) {

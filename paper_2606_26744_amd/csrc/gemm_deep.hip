@@ -472,6 +472,43 @@ __device__ __forceinline__ void store_rows(const f32x16_t (&acc)[TM][TN], const 
   }
 }
 
+// The gated activation SiLU(gate) * up in bf16 from the transposed product: the first half of a
+// wave's blocks are gate columns and the second half the same columns' up part, so that both
+// meet in a lane.  Rows leave through a region of LDS of the wave's own, as in store_rows.
+template <int TM, int TN>
+__device__ __forceinline__ void store_gated(const f32x16_t (&acc)[TM][TN], const GemmArgs& p, int m0,
+                                            int c0, bf16_t* lds) {
+  constexpr int W = 16 * TN, LD = W + 8;        // columns of a wave, padded LDS row
+  constexpr int PER = W / 8, RPI = 64 / PER;    // 16-byte pieces of a row, rows a store
+  const int lane = threadIdx.x & 63, h = lane >> 5, tok = lane & 31;
+  bf16_t* own = lds + (threadIdx.x >> 6) * 32 * LD;
+  bf16_t* out = static_cast<bf16_t*>(p.out);
+  const int F = p.N / 2;
+  lds_barrier();   // the K loop's last reads
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int t = 0; t < TN / 2; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x16_t &a = acc[i][t], &b = acc[i][t + TN / 2];
+        *reinterpret_cast<uint2*>(own + tok * LD + 32 * t + 8 * g + 4 * h) =
+            make_uint2(pack_bf2(silu_mul(a[4 * g], b[4 * g]), silu_mul(a[4 * g + 1], b[4 * g + 1])),
+                       pack_bf2(silu_mul(a[4 * g + 2], b[4 * g + 2]), silu_mul(a[4 * g + 3], b[4 * g + 3])));
+        HDF_PIN();
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 32 / RPI; ++q) {
+      const int r = q * RPI + lane / PER, c = (lane % PER) * 8;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(own + r * LD + c);
+      const int row = m0 + 32 * i + r, col = c0 + c;
+      if (row < p.M && col < F) st16(out + int64_t(row) * F + col, v);   // F is a multiple of 64
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 template <int TM, int TN, int EPI>
 __global__ void __launch_bounds__(kDeepThreads, 1)
 gemm_deep_kernel(GemmArgs p) {
@@ -517,6 +554,20 @@ gemm_deep_kernel(GemmArgs p) {
   const BufRsrc ra = buf_rsrc(A, int((int64_t(min(BM, p.M - m0) - 1) * p.lda + p.K) * 2));
   const BufRsrc rb = buf_rsrc(B, k1 * 2 * 8192);
   const int off = (blk0 & 3) * 1024;
+  // kEpiGated: a tile is BN / 2 gate columns and the same up columns; the wave's gate blocks
+  // start at block gb, its up blocks F/32 blocks on (F is a multiple of 64, so two blocks of
+  // one kind are in one 128-row group).  Blocks past F are clamped and never stored.
+  BufRsrc rb0 = rb, rb1 = rb;
+  int off0 = off, off1 = off + TN / 2 * 1024;
+  if constexpr (EPI == kEpiGated) {
+    const int fb = p.N / 64;
+    const int gb = min((n_tile * 4 + wid) * (TN / 2), fb - TN / 2), ub = gb + fb;
+    const bf16_t* W = static_cast<const bf16_t*>(p.B);
+    rb0 = buf_rsrc(W + int64_t(gb >> 2) * (p.K >> 4) * 2048, k1 * 2 * 8192);
+    rb1 = buf_rsrc(W + int64_t(ub >> 2) * (p.K >> 4) * 2048, k1 * 2 * 8192);
+    off0 = (gb & 3) * 1024;
+    off1 = (ub & 3) * 1024;
+  }
   f32x16_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -548,7 +599,7 @@ gemm_deep_kernel(GemmArgs p) {
   }
   constexpr bool SWAP = EPI != kEpiPartial;
   if (k1 > k0)
-    deep_loop<TM, TN, SWAP>(acc, ra, p.lda, rb, off, rb, off + TN / 2 * 1024, k0 * 2, (k1 - k0) * 2, lds);
+    deep_loop<TM, TN, SWAP>(acc, ra, p.lda, rb0, off0, rb1, off1, k0 * 2, (k1 - k0) * 2, lds);
   if constexpr (EPI == kEpiKV) {
     // d is a multiple of the tile's 512 columns, so a tile lies wholly in K or in V.
     if (n0 < p.kv_d)
@@ -557,6 +608,8 @@ gemm_deep_kernel(GemmArgs p) {
       store_values(acc, p, c0 - p.kv_d, row_tab);
   } else if constexpr (EPI == kEpiArgmax) {
     fold_argmax<TM, TN>(acc, p, m0, c0, reinterpret_cast<float*>(smem));
+  } else if constexpr (EPI == kEpiGated) {
+    store_gated<TM, TN>(acc, p, m0, (n_tile * 4 + wid) * 16 * TN, reinterpret_cast<bf16_t*>(smem));
   } else if constexpr (EPI == kEpiRows) {
     store_rows<TM, TN>(acc, p, m0, c0, reinterpret_cast<bf16_t*>(smem));
   } else {
@@ -593,6 +646,8 @@ hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hi
     launch_deep<4, 4, kEpiArgmax>(a, 1, s);
   else if (epi == kEpiRows)
     launch_tile<kEpiRows>(a, plan, 1, s);
+  else if (epi == kEpiGated)
+    launch_tile<kEpiGated>(a, plan, 1, s);
   else
     launch_tile<kEpiPartial>(a, plan, plan.splits, s);
   return hipGetLastError();
@@ -608,18 +663,17 @@ hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hi
 // them (1024 x 4096 -> 24576 in two splits: 180 against 212 us; -> 129280 862 against 938),
 // 128 x 512 above, whose fragments cost half the LDS reads (16384 x 4096 -> 8192: 815 against
 // 820 us, 16384 x 16384 -> 4096 1520 against 1553), unless the other one takes fewer rounds.
-GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
+static GemmPlan deep_plan(int M, int N, int M2, int N2, int K, int max_splits, double part, double* time) {
   const int ncu = device_cu_count();
   const int nk = K / 64;
   const bool tall = M > 2048 || M2 > 2048;
   struct Shape { int bm, tn; double unit; };
   const Shape shapes[3] = {{tall ? 128 : 256, tall ? 4 : 2, 0.72}, {tall ? 256 : 128, tall ? 2 : 4, 0.73},
                            {128, 2, 0.415}};
-  const double part = (double(M) * N + double(M2) * N2) * 8.0 / 5.2e6;
   GemmPlan best{4, 1, 2};
   best.bm = 256;
   double best_t = 1e30;
-  for (int sp = 1; sp <= 8 && (sp == 1 || nk / sp >= 8); ++sp)
+  for (int sp = 1; sp <= max_splits && (sp == 1 || nk / sp >= 8); ++sp)
     for (const Shape& x : shapes) {
       const int bn = 128 * x.tn;
       const int64_t tiles = ((int64_t(M) + x.bm - 1) / x.bm) * ((N + bn - 1) / bn) +
@@ -632,7 +686,23 @@ GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
         best.bm = x.bm;
       }
     }
+  if (time != nullptr) *time = best_t;
   return best;
+}
+
+GemmPlan deep_plan(int M, int N, int M2, int N2, int K) {
+  return deep_plan(M, N, M2, N2, K, 8, (double(M) * N + double(M2) * N2) * 8.0 / 5.2e6, nullptr);
+}
+
+// The gate and up product with its activation in the epilogue (one K split, no partials): taken
+// where its estimate is below that of partial sums and the pass over them (about 4 us and the
+// partials' reads, which deep_plan counts).  1024 rows of 4096, 12288 wide: 175 + 19 -> 179 us;
+// a few hundred rows of a narrow drafter leave most CUs without a tile in one split.
+bool deep_gated_plan(int M, int F, int K, GemmPlan* plan) {
+  double one = 0.0, split = 0.0;
+  *plan = deep_plan(M, 2 * F, 0, 0, K, 1, 0.0, &one);
+  (void)deep_plan(M, 2 * F, 0, 0, K, 8, double(M) * 2 * F * 8.0 / 5.2e6, &split);
+  return one < split + 4.0;
 }
 
 // The LM head's tile: 256 x 256, whose weights half as many row tiles re-read from HBM (8 to

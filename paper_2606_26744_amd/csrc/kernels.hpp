@@ -42,6 +42,7 @@ constexpr int kEpiPartial = 0;  // fp32 C / split-K partials
 constexpr int kEpiArgmax = 1;   // LM head: fused row argmax (+ optional fp32 logits in C)
 constexpr int kEpiKV = 2;       // context K/V rows: RoPE on K, stored into the cache layouts
 constexpr int kEpiRows = 3;     // bf16 rows (+ bias), one K split
+constexpr int kEpiGated = 4;    // SiLU(gate) * up in bf16, one K split
 
 struct GemmArgs {
   const void* A;   // [M][lda] row-major activations
@@ -67,6 +68,7 @@ struct GemmArgs {
   int64_t cap;
   int kv_d, hd;
   // kEpiRows: out[M][N] bf16 (16-byte aligned), N % 4 == 0; bias [N] fp32 or NULL.
+  // kEpiGated: W the stacked [gate; up], out[M][N/2] bf16, N/2 a multiple of 64.
   void* out;
   const float* bias;
 };
@@ -91,6 +93,7 @@ GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K);
 // `epi` (kEpiPartial by the plan's splits, the others in one).
 GemmPlan deep_plan(int M, int N, int M2, int N2, int K);
 GemmPlan deep_argmax_plan(int M);
+bool deep_gated_plan(int M, int F, int K, GemmPlan* plan);   // false: partial sums are faster
 hipError_t launch_gemm_deep(int epi, const GemmArgs& a, const GemmPlan& plan, hipStream_t s);
 size_t packed_weight_elems(int N, int K);          // rows rounded up to 128
 hipError_t launch_pack_weight(bool bf16, const void* src, void* dst, int N, int K, hipStream_t s);
@@ -105,6 +108,11 @@ hipError_t launch_gemm_partial2(const void* A, int64_t lda, const void* B, int M
 // (returns hipErrorInvalidValue otherwise).
 hipError_t launch_gemm_rows(const void* A, int64_t lda, const void* B, int M, int N, int K,
                             GemmPlan plan, const float* bias, void* out, hipStream_t s);
+// act[M][F] (bf16) = SiLU(A . Wg^T) * (A . Wu^T), W [2F][K] the stacked [gate; up] weights: for
+// more than 128 rows where it beats partial sums (returns false otherwise).
+bool gemm_gated_plan(int M, int F, int K, GemmPlan* plan);
+hipError_t launch_gemm_gated(const void* A, int64_t lda, const void* W, int M, int F, int K,
+                             GemmPlan plan, void* act, hipStream_t s);
 // Context K/V projection straight into the cache: A [M][d] normed context rows (bf16),
 // B the packed W_k; W_v rows (2d x d), RoPE on K at plan_pos, stores at plan_row.  Only
 // for plans of one K split and two-block waves and d % 512 == 0 (returns

@@ -326,3 +326,14 @@ def test_cold_rows_stored_by_the_projection(hd, ctx, new, rope):
     assert sum(new) > 2048
     _compare(DraftCase(wl, ctx, new, sub=41, rope=rope))
     _compare(DraftCase(wl, ctx, new, sub=42, rope=rope, paged=True, spare_pages=2))
+
+
+@pytest.mark.parametrize("n_seq,B,d,F", [(9, 16, 512, 1024), (13, 20, 512, 704), (40, 16, 1024, 192)])
+def test_gated_product_above_128_rows(n_seq, B, d, F):
+    """More than 128 block rows: the activation of the gate and up product in its epilogue, with
+    ragged last row and column tiles (F an odd multiple of 64 among them)."""
+    wl = synth.small_bf16()
+    wl.d = d
+    wl.drafter = synth.DrafterShape(d=d, n_layers=1, n_heads=d // 64, head_dim=64, d_ff=F, vocab=600)
+    ctx = [40 + 7 * s for s in range(n_seq)]
+    _compare(DraftCase(wl, ctx, [3] * n_seq, B=B, sub=51), seqs=[0, n_seq // 2, n_seq - 1])
