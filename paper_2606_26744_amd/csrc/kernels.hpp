@@ -115,7 +115,7 @@ hipError_t launch_gemm_gated(const void* A, int64_t lda, const void* W, int M, i
                              GemmPlan plan, void* act, hipStream_t s);
 // Context K/V projection straight into the cache: A [M][d] normed context rows (bf16),
 // B the packed W_k; W_v rows (2d x d), RoPE on K at plan_pos, stores at plan_row.  Only
-// for plans of one K split and two-block waves and d % 512 == 0 (returns
+// for plans of one K split on the matrix-core bound tiles and d % 512 == 0 (returns
 // hipErrorInvalidValue otherwise).
 hipError_t launch_gemm_kv(const void* A, int64_t lda, const void* B, int M, int d, int hd,
                           GemmPlan plan, const int32_t* plan_pos, const int32_t* plan_row,
