@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <initializer_list>
 #include <mutex>
@@ -278,7 +279,10 @@ hdf_status hdf_fc_reduce(const void* H, const void* W_fc, const float* b_fc, int
   float* parts = static_cast<float*>(ws);
   for (int64_t r0 = 0; r0 < n_tok; r0 += kFcChunk) {
     const int rows = int(n_tok - r0 < kFcChunk ? n_tok - r0 : kFcChunk);
-    const hdf::GemmPlan pl = hdf::gemm_plan(bf, rows, d, K);
+    hdf::GemmPlan pl = hdf::gemm_plan(bf, rows, d, K);
+    // A last chunk of fewer rows may plan more splits than the workspace, which is sized by the
+    // whole chunks, has room for; one split of it always fits.
+    pl.splits = int(std::min<size_t>(size_t(pl.splits), need / (size_t(rows) * size_t(d) * 4)));
     if (bf && pl.tn > 1 && pl.splits == 1) {
       // One K split on the matrix-core bound tiles: bias, rounding and the rows' stores happen
       // in the product's epilogue (the fp32 rows and the pass over them took 83 us of 1679 at

@@ -50,6 +50,28 @@ def test_rows_past_one_chunk():
     _case(16384 + 100, 2, 256, "bf16", 3)
 
 
+@pytest.mark.parametrize("rest,m,d,dtype", [(8634, 4, 64, "f32"), (5724, 4, 576, "bf16")])
+def test_last_chunk_stays_in_the_workspace(rest, m, d, dtype):
+    """A last chunk whose own plan takes more split partials than the whole chunks' workspace
+    holds: nothing is written past the workspace's stated size."""
+    n = 16384 + rest
+    code = hdf.HDF_F32 if dtype == "f32" else hdf.HDF_BF16
+    need = int(hdf.lib().hdf_fc_reduce_workspace(n, m, d, code))
+    assert int(hdf.lib().hdf_fc_reduce_workspace(rest, m, d, code)) > need   # the case is that case
+    H = synth.normal([n, m, d], 1.0, 5, 70, dtype=dtype, device="cuda")
+    W = synth.normal([d, m * d], 0.02, 5, 71, dtype=dtype, device="cuda")
+    buf = torch.full((need * 4,), 0x5A, dtype=torch.uint8, device="cuda")   # ends past any plan
+    Y = hdf.fc_reduce(H, hdf.pack_weight(W), ws=buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    ref = ref_fc(synth.to_numpy_bits(H), synth.to_numpy_bits(W), None, dtype=dtype)
+    got = synth.to_numpy_bits(Y)
+    if dtype == "bf16":
+        assert_bf16_close(as_f64(got), ref, "Y")
+    else:
+        assert_f32_rows_close(got, ref, "Y")
+
+
 def test_block_identity_weights_sum_the_paths():
     """W_fc = [I I I I] sums the paths exactly as the gated reducer with unit gates."""
     n, m, d = 64, 4, 512
