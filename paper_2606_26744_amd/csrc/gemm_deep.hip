@@ -17,8 +17,9 @@
 // in the order it is written here (a scheduling fence after each): the compiler's own order
 // sank the fragment reads to their uses, an exposed LDS round trip every four MFMAs.
 // Addresses cost no vector instructions: buffer loads with a per-lane offset computed once
-// and the unit in the scalar offset; the descriptors end at the operands' last row or unit,
-// so rows past M and units past K read as zero without a fetch.
+// and the unit in the scalar offset.  The activations' descriptor ends at the last row, so rows
+// past M (a lane offset past its end) read as zero without a fetch; units past K, which the ring
+// issues and nothing uses, re-read the last one (deep_schedule.hpp).
 //
 // Measured alone (random operands, warm): 16384 x 4096 -> 8192 972 -> 815 us with fp32 stores,
 // 16384 x 16384 -> 4096 1878 -> 1520 us, 1024 x 4096 -> 24576 in two K splits 204 -> 180 us,
@@ -27,13 +28,13 @@
 // 779, fp32 rows 837.  Copies without stores run at 1.40-1.52 PFLOP/s, without any load from memory in
 // the loop at 1.60-1.72, the MFMAs alone at 1.67-1.80 (the power limit on such data).
 #include "common.hpp"
+#include "deep_schedule.hpp"
 #include "gemm_tile.hpp"
 #include "kernels.hpp"
 
 namespace hdf {
 
 constexpr int kDeepThreads = 256;
-constexpr int kDeepRing = 4;     // weight units in the register ring
 // Row tiles of one group in the tile order of tall problems: consecutive tile ids walk four
 // row tiles of a column block, then the next column block, so that the 32 tiles an XCD runs
 // share activation and weight slices in its L2 (16384 x 4096 -> 8192: 4 row tiles 846 us, 8
@@ -101,12 +102,11 @@ __device__ __forceinline__ void deep_loop(f32x16_t (&acc)[TM][TN], const BufRsrc
   u32x4 rb[R][2][TN];
   u32x4 ra[2][PCH];
   const int np = nu / 2;
-  // Pairs past the end re-read the last one (never used); units past the end read zeros.
   auto a_load = [&](int pr, int j, u32x4* dst) {
-    dst[j] = buf_ld16(ra_, av[j], (ku0 / 2 + min(pr, np - 1)) * 128);
+    dst[j] = buf_ld16(ra_, av[j], deep_act_offset(ku0, pr, np));
   };
   auto b_load = [&](int u, int ss, int t, u32x4 (*dst)[TN]) {
-    const int at = (ku0 + u) * 8192 + ss * 4096;
+    const int at = deep_weight_offset(ku0, u, nu, ss);
     dst[ss][t] = t < TN / 2 ? buf_ld16(rb0, bv0 + t * 1024, at) : buf_ld16(rb1, bv1 + (t - TN / 2) * 1024, at);
   };
   auto a_store = [&](const u32x4* src, int j, int buf) {
@@ -554,7 +554,7 @@ gemm_deep_kernel(GemmArgs p) {
   const bf16_t* A = static_cast<const bf16_t*>(p.A) + int64_t(m0) * p.lda;
   const bf16_t* B = static_cast<const bf16_t*>(p.B) + int64_t(grp) * (p.K >> 4) * 2048;
   const BufRsrc ra = buf_rsrc(A, int((int64_t(min(BM, p.M - m0) - 1) * p.lda + p.K) * 2));
-  const BufRsrc rb = buf_rsrc(B, k1 * 2 * 8192);
+  const BufRsrc rb = buf_rsrc(B, deep_weight_bytes(k1));
   const int off = (blk0 & 3) * 1024;
   // kEpiGated: a tile is BN / 2 gate columns and the same up columns; the wave's gate blocks
   // start at block gb, its up blocks F/32 blocks on (F is a multiple of 64, so two blocks of
@@ -565,8 +565,8 @@ gemm_deep_kernel(GemmArgs p) {
     const int fb = p.N / 64;
     const int gb = min((n_tile * 4 + wid) * (TN / 2), fb - TN / 2), ub = gb + fb;
     const bf16_t* W = static_cast<const bf16_t*>(p.B);
-    rb0 = buf_rsrc(W + int64_t(gb >> 2) * (p.K >> 4) * 2048, k1 * 2 * 8192);
-    rb1 = buf_rsrc(W + int64_t(ub >> 2) * (p.K >> 4) * 2048, k1 * 2 * 8192);
+    rb0 = buf_rsrc(W + int64_t(gb >> 2) * (p.K >> 4) * 2048, deep_weight_bytes(k1));
+    rb1 = buf_rsrc(W + int64_t(ub >> 2) * (p.K >> 4) * 2048, deep_weight_bytes(k1));
     off0 = (gb & 3) * 1024;
     off1 = (ub & 3) * 1024;
   }
