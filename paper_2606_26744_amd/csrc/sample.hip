@@ -57,26 +57,38 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64
   for (int j = 0; j < 4; ++j) c[j] = uint64_t(v[2 * j]) | (uint64_t(v[2 * j + 1]) << 32);
 }
 
-// Uniforms of the eight entries 8*g .. 8*g+7 of one row.
-__device__ __forceinline__ void uniforms8(uint64_t seed, uint64_t stream, uint64_t row, uint64_t g,
-                                          int purpose, float u[8]) {
+// The 24-bit draws k of the eight entries 8*g .. 8*g+7 of one row; entry uniform u = (k + 1/2) / 2^24.
+__device__ __forceinline__ void draws8(uint64_t seed, uint64_t stream, uint64_t row, uint64_t g,
+                                       int purpose, uint32_t k[8]) {
   uint64_t c[4] = {row, g, uint64_t(purpose), 0ull};
   philox4x64_10(c, seed, stream);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    u[2 * j] = (float(uint32_t(c[j] >> 40)) + 0.5f) * 5.9604644775390625e-8f;
-    u[2 * j + 1] = (float(uint32_t(c[j] & 0xFFFFFFFFull) >> 8) + 0.5f) * 5.9604644775390625e-8f;
+    k[2 * j] = uint32_t(c[j] >> 40);
+    k[2 * j + 1] = uint32_t(c[j] & 0xFFFFFFFFull) >> 8;
   }
+}
+
+// u rounded to fp32: up to 2^-25 off, and 1 for the greatest.
+__device__ __forceinline__ float uniform(uint32_t k) {
+  return (float(k) + 0.5f) * 5.9604644775390625e-8f;
+}
+// -log2(u).  The rounding of k + 1/2 (from 2^23 on) would change it by up to 2^-25 / (1 - u) of
+// itself, a third at the greatest uniforms and all of it at the last, whose column would win the
+// draw whatever its probability: what the sum lost is taken off to first order.
+__device__ __forceinline__ float neg_log2_uniform(uint32_t k) {
+  const float a = float(k), s = a + 0.5f;
+  const float lost = (a - s) + 0.5f;   // exact: 0 or +-1/2
+  return fmaf(lost, -8.5991325e-8f, fabsf(__builtin_amdgcn_logf(s * 5.9604644775390625e-8f)));
 }
 
 constexpr int kGroupsPerPass = 4;   // 8-entry groups each thread loads before computing
 
 // The draw as a race: argmax_v (s_v - log(-log u_v)) is argmax_v e^(s_v - m) / -log2(u_v)
 // for any m, so the entries compare by this ratio, whose numerator the log-sum-exp needs
-// anyway, and only a thread's winner takes a logarithm of it.  u = 1 (the top draw, rounded)
-// wins with an infinite ratio, as it does with an infinite score.
-__device__ __forceinline__ float race(float p, float u) {
-  return p * __builtin_amdgcn_rcpf(fabsf(__builtin_amdgcn_logf(u)));
+// anyway, and only a thread's winner takes a logarithm of it.
+__device__ __forceinline__ float race(float p, uint32_t k) {
+  return p * __builtin_amdgcn_rcpf(neg_log2_uniform(k));
 }
 // Perturbed score s_v - log(-log u_v) of a ratio with numerator e^(s_v - m).
 __device__ __forceinline__ float race_score(float ratio, float m) {
@@ -197,8 +209,8 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
       st.s = st.s * down + add;
       st.m = mn;
       if constexpr (SAMPLE) {
-        float u[8];
-        uniforms8(seed, stream, uint64_t(row), uint64_t(g), kPurposeDraft, u);
+        uint32_t dr[8];
+        draws8(seed, stream, uint64_t(row), uint64_t(g), kPurposeDraft, dr);
         // The group's best ratio, lowest index first (entries past the end have p = 0, the
         // group's largest p = 1 or a running maximum above it); groups come in increasing
         // order, so a tie with the running best keeps the running (lower) index.
@@ -206,12 +218,12 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
         int gk = 0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          const float r = race(p[k], u[k]);
+          const float r = race(p[k], dr[k]);
           const bool take = r > gb;
           gb = take ? r : gb;
           gk = take ? k : gk;
         }
-        ratio = ratio == INFINITY ? ratio : ratio * down;
+        ratio *= down;
         if (gb > ratio) {
           ratio = gb;
           st.idx = 8 * g + gk;
@@ -332,9 +344,11 @@ accept_decide_kernel(const int32_t* __restrict__ draft, int draft_stride,
       const int x = draft[dr];
       const float q = __expf(draft_logits[dr * ld + x] * inv_t - draft_lse[dr]);
       const float p = __expf(target_logits[(t0 + i) * V + x] * inv_t - lse[i]);
-      float u[8];
-      uniforms8(seed, stream, uint64_t(s), uint64_t(i >> 3), kPurposeAccept, u);
-      reject = !(u[i & 7] * q < p);
+      uint32_t dk[8];
+      draws8(seed, stream, uint64_t(s), uint64_t(i >> 3), kPurposeAccept, dk);
+      // Below 1 also after rounding, so that a draft with q = p is never rejected.
+      const float u = fminf(uniform(dk[i & 7]), 1.f - 5.9604644775390625e-8f);
+      reject = !(u * q < p);
     }
     const unsigned long long m = __ballot(reject);
     if (m != 0ull) {
@@ -396,16 +410,16 @@ accept_draw_kernel(const float* __restrict__ draft_logits, const float* __restri
         if (resid && k < nv) d[k] = zd[v0 + k];
       }
     }
-    float u[8];
-    uniforms8(seed, stream, uint64_t(s), uint64_t(g), kPurposeResample, u);
+    uint32_t dk[8];
+    draws8(seed, stream, uint64_t(s), uint64_t(g), kPurposeResample, dk);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       if (k < nv) {
         const float p = __expf(t[k] * inv_t - lt);
         const float w = resid ? p - __expf(d[k] * inv_t - ldr) : p;
-        const unsigned long long key = sample_key(race(w, u[k]), v0 + k);
+        const unsigned long long key = sample_key(race(w, dk[k]), v0 + k);
         if (w > 0.f && key > ka) ka = key;
-        const unsigned long long fall = sample_key(race(p, u[k]), v0 + k);
+        const unsigned long long fall = sample_key(race(p, dk[k]), v0 + k);
         if (resid && p > 0.f && fall > kb) kb = fall;
       }
     }

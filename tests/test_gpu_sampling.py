@@ -9,7 +9,8 @@ import torch
 
 import synth
 from oracle.lm_head import lm_head_logits
-from oracle.sampling import accept_sample as ref_accept_sample, sample_tokens as ref_sample
+from oracle.sampling import (PURPOSE_DRAFT, PURPOSE_RESAMPLE, accept_sample as ref_accept_sample, gumbel,
+                             sample_tokens as ref_sample, uniforms)
 from paper_2606_26744_amd import hdf
 
 pytestmark = pytest.mark.gpu
@@ -151,3 +152,50 @@ def test_sample_tokens_masked_columns():
     ok = margin >= SMARGIN
     assert np.array_equal(tok.cpu().numpy()[ok], r_tok[ok])
     np.testing.assert_allclose(lse.cpu().numpy(), r_lse, rtol=1e-5, atol=1e-5)
+
+
+# The greatest of the 2^24 uniforms is 1 - 2^-25, which fp32 rounds to 1.
+TOP_U = 1.0 - 2.0 ** -25
+
+
+@pytest.mark.parametrize("lead", [-25.0, -0.02, 0.02])
+def test_sample_tokens_top_uniform(lead):
+    """A column with the greatest uniform wins by its score (noise 17.3) and not whatever its
+    logit: far below the other columns, and just short and just ahead of the best of them."""
+    V, seed, rows, cols = 129280, 15, [9, 12], [75613, 108433]
+    lg = _logits(13, V, 23)
+    for r, c in zip(rows, cols):
+        g = gumbel(uniforms(seed, 0, r, np.arange(V), PURPOSE_DRAFT))
+        assert g[c] == gumbel(np.float64(TOP_U))
+        score = lg[r].cpu().numpy().astype(np.float64) + g
+        score[c] = -np.inf
+        lg[r, c] = float(score.max() - g[c] + lead)
+    tok, _ = _check_sample(lg, 1.0, seed=seed, stream=0, rows=rows)
+    tok = tok.cpu().numpy()
+    assert [int(tok[r]) == c for r, c in zip(rows, cols)] == [lead > 0] * 2
+
+
+@pytest.mark.parametrize("lead", [-25.0, -0.02, 0.02])
+def test_accept_sample_top_uniform(lead):
+    """The same for the token drawn after the decisions (here the bonus of blocks without
+    drafts)."""
+    n, V, seed, rows, cols = 8, 129280, 55, [0, 6], [49204, 44808]
+    lg = _logits(n, V, 29)
+    for s, c in zip(rows, cols):
+        g = gumbel(uniforms(seed, 9, s, np.arange(V), PURPOSE_RESAMPLE))
+        assert g[c] == gumbel(np.float64(TOP_U))
+        score = lg[s].cpu().numpy().astype(np.float64) + g
+        score[c] = -np.inf
+        lg[s, c] = float(score.max() - g[c] + lead)
+    tok = torch.zeros(n, dtype=torch.int32, device="cuda")
+    lse = torch.zeros(n, dtype=torch.float32, device="cuda")
+    _, anc, _, _ = hdf.accept_sample(tok, lg, lse, lg.view(n, 1, V), K=0, draft_stride=1, ld=V,
+                                     temperature=1.0, seed=seed, stream_id=9)
+    torch.cuda.synchronize()
+    _, r_anc, _, _, _, smarg = ref_accept_sample(np.zeros((n, 0), dtype=np.int32),
+                                                 np.zeros((n, 0, V)), lg.cpu().numpy().reshape(n, 1, V),
+                                                 1.0, seed, 9)
+    anc = anc.cpu().numpy()
+    ok = smarg >= SMARGIN
+    assert ok[rows].all() and np.array_equal(anc[ok], r_anc[ok])
+    assert [int(anc[s]) == c for s, c in zip(rows, cols)] == [lead > 0] * 2
