@@ -223,10 +223,21 @@ row_pass_kernel(const float* __restrict__ logits, int64_t ld, int V, int n_parts
           gb = take ? r : gb;
           gk = take ? k : gk;
         }
-        ratio *= down;
-        if (gb > ratio) {
-          ratio = gb;
-          st.idx = 8 * g + gk;
+        if (mn < INFINITY) {
+          ratio *= down;
+          if (gb > ratio) {
+            ratio = gb;
+            st.idx = 8 * g + gk;
+          }
+        } else if (ratio < INFINITY) {
+          // A scaled logit beyond fp32 (a temperature near 0): the first one wins, as an
+          // infinite score does; its numerator is e^(inf - inf).
+#pragma unroll
+          for (int k = 7; k >= 0; --k)
+            if (p[k] != p[k]) {
+              ratio = INFINITY;
+              st.idx = 8 * g + k;
+            }
         }
       }
     }

@@ -199,3 +199,19 @@ def test_accept_sample_top_uniform(lead):
     ok = smarg >= SMARGIN
     assert ok[rows].all() and np.array_equal(anc[ok], r_anc[ok])
     assert [int(anc[s]) == c for s, c in zip(rows, cols)] == [lead > 0] * 2
+
+
+@pytest.mark.parametrize("V", [8, 1001, 40000])
+def test_sample_tokens_scaled_logits_beyond_fp32(V):
+    """A temperature so near 0 that logits / T overflow: the first column whose scaled logit is
+    infinite is drawn (an infinite score), wherever it lies."""
+    T = 2e-38
+    lg = _logits(5, V, V) - 4.0
+    lg[lg > 0] *= -1.0
+    at = torch.tensor([0, 1, V // 2, V - 2, V - 1])
+    lg[torch.arange(5, device="cuda"), at.cuda()] = 7.0
+    lg[2, V // 2 + 1] = 9.0
+    tok, _ = hdf.sample_tokens(lg, temperature=T, seed=4, stream_id=1)
+    torch.cuda.synchronize()
+    assert torch.isinf(torch.tensor(7.0) * torch.tensor(1.0 / T, dtype=torch.float32))
+    assert torch.equal(tok.cpu().long(), at)
