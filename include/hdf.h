@@ -102,7 +102,9 @@ hdf_status hdf_hc_reduce(const void* H, const void* W_g, const float* b_g, int64
  * with no normalisation (about 67M parameters at m = 4, d = 4096, against the gated
  * reducer's 65K).  Accumulation in fp32, Y rounded to `dtype`.
  * ----------------------------------------------------------------------------*/
-/* Workspace bytes of hdf_fc_reduce (0 on invalid arguments). */
+/* Workspace bytes of hdf_fc_reduce (0 on invalid arguments).  Up to 16384 rows the size grows
+ * with n_tok, so that one workspace serves every smaller call; more rows run in chunks of 16384,
+ * and the size reported for them is that of such calls only. */
 size_t hdf_fc_reduce_workspace(int64_t n_tok, int m, int d, hdf_dtype dtype);
 /* H     [n_tok][m][d] dtype
  * W_fc  [d][m*d] dtype, packed (hdf_pack_weight with N = d, K = m*d)
@@ -230,7 +232,8 @@ hdf_status hdf_kv_read_rows(const void* kv_k, const void* kv_vt, int64_t kv_cap,
                             int64_t row0, int64_t n_rows, void* k_rows, void* v_rows,
                             hdf_stream_t stream);
 
-/* Workspace bytes hdf_draft_block needs for these sizes (0 on invalid arguments). */
+/* Workspace bytes hdf_draft_block needs for these sizes (0 on invalid arguments), and for the
+ * same ones with fewer new rows: one workspace, sized by the largest n_new, serves all rounds. */
 size_t hdf_draft_block_workspace(const hdf_drafter* w, int n_seq, int B, int64_t n_new,
                                  int max_ctx);
 

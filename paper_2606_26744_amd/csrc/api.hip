@@ -107,7 +107,28 @@ struct DraftPlan {
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-DraftPlan plan_workspace(const hdf_drafter& w, int n_seq, int B, int64_t n_new, int max_ctx) {
+// Bytes of the split partials of a product over 1 .. rows rows, at most: the K splits fall with
+// the rows as long as the count of row tiles stays (a split's partials cost more, nothing else
+// changes), so a block of rows within one tile count needs no more than its first row's splits
+// over its last row's partials.  `base` rows of the same problem precede the counted ones; a row
+// has `per_row` columns, and `fixed` more elements go with every split.
+template <typename Splits>
+size_t parts_upto(int64_t rows, int64_t base, bool bf, size_t per_row, size_t fixed, Splits splits) {
+  size_t most = 0;
+  for (int64_t b = rows; b > 0;) {   // the blocks from the last one down
+    const size_t one = (size_t(b) * per_row + fixed) * 4;
+    if (one * hdf::kMaxSplits <= most) break;
+    const int64_t step = !bf ? 32 : b + base <= 128 ? 64 : 128;   // row tiles are multiples of it
+    const int64_t before = std::max<int64_t>(0, (b + base - 1) / step * step - base);
+    most = std::max(most, one * size_t(splits(before + 1)));
+    b = before;
+  }
+  return most;
+}
+
+// upto: room for every call of at most n_new rows (the size that is reported), else for this one.
+DraftPlan plan_workspace(const hdf_drafter& w, int n_seq, int B, int64_t n_new, int max_ctx,
+                         bool upto) {
   DraftPlan P{};
   const bool bf = w.dtype == HDF_BF16;
   const size_t el = bf ? 2 : 4;
@@ -159,6 +180,21 @@ DraftPlan plan_workspace(const hdf_drafter& w, int n_seq, int B, int64_t n_new, 
     const size_t sp = size_t(hdf::gemm_plan2(bf, int(n_new), 2 * w.d, int(M), 3 * w.d, w.d).splits);
     const size_t b = sp * (size_t(n_new) * 2 * w.d + M * 3 * w.d) * 4;
     if (b > parts) parts = b;
+  }
+  if (upto) {
+    const int iM = int(M);
+    const size_t kv = 2 * d, blk = M * 3 * d;
+    parts = std::max(parts, parts_upto(crow, 0, bf, kv, 0, [&](int64_t r) {
+              return hdf::gemm_plan(bf, int(r), 2 * w.d, w.d).splits;
+            }));
+    if (bf)
+      parts = std::max(parts, parts_upto(std::min(n_new, kGroupRows), 0, bf, kv, blk, [&](int64_t r) {
+                return hdf::gemm_plan2(bf, int(r), 2 * w.d, iM, 3 * w.d, w.d).splits;
+              }));
+    if (kv_shared(bf, 1, M))
+      parts = std::max(parts, parts_upto(std::min<int64_t>(n_new, 128), iM, bf, kv, blk, [&](int64_t r) {
+                return hdf::gemm_plan_shared(int(r) + iM, 2 * w.d, iM, w.d, w.d).splits;
+              }));
   }
   upd(int64_t(M), 3 * w.d, w.d);
   upd(int64_t(M), w.d, w.d);
@@ -248,7 +284,13 @@ static size_t fc_parts_bytes(int64_t n_tok, int m, int d, hdf_dtype dtype) {
 
 size_t hdf_fc_reduce_workspace(int64_t n_tok, int m, int d, hdf_dtype dtype) {
   if (n_tok < 0 || !fc_shape_ok(m, d, dtype)) return 0;
-  return (fc_parts_bytes(n_tok, m, d, dtype) + 255) / 256 * 256;
+  size_t need = fc_parts_bytes(n_tok, m, d, dtype);
+  const bool bf = dtype == HDF_BF16;
+  if (n_tok <= kFcChunk)   // room for every smaller call
+    need = std::max(need, parts_upto(n_tok, 0, bf, size_t(d), 0, [&](int64_t r) {
+                      return hdf::gemm_plan(bf, int(r), d, m * d).splits;
+                    }));
+  return (need + 255) / 256 * 256;
 }
 
 hdf_status hdf_fc_reduce(const void* H, const void* W_fc, const float* b_fc, int64_t n_tok, int m,
@@ -520,7 +562,7 @@ size_t hdf_draft_block_workspace(const hdf_drafter* w, int n_seq, int B, int64_t
                                  int max_ctx) {
   if (validate_drafter(w) != HDF_OK || n_seq < 0 || B < 1 || B > 64 || n_new < 0 || max_ctx < 0)
     return 0;
-  return plan_workspace(*w, n_seq, B, n_new, max_ctx).total;
+  return plan_workspace(*w, n_seq, B, n_new, max_ctx, true).total;
 }
 
 // Both cache forms: kv_offsets (contiguous slots) or page_table (pages of 64 rows; the
@@ -559,7 +601,7 @@ static hdf_status draft_block_impl(const hdf_drafter* w, int n_seq, int B, const
   if (!aligned16(hidden) || (y_new && !aligned16(y_new)) || (kv_k && !aligned16(kv_k)) ||
       (kv_vt && !aligned16(kv_vt)))
     return fail(HDF_E_INVALID, "draft_block: tensors must be 16-byte aligned");
-  const DraftPlan P = plan_workspace(*w, n_seq, B, n_new, max_ctx);
+  const DraftPlan P = plan_workspace(*w, n_seq, B, n_new, max_ctx, false);
   if (ws == nullptr || ws_bytes < P.total)
     return fail(HDF_E_WORKSPACE, "draft_block: workspace of %zu bytes needed, %zu given", P.total,
                 ws_bytes);

@@ -489,9 +489,10 @@ static GemmPlan f32_plan(int M, int N, int K, int max_splits) {
     const int BM = 32 * tn;
     const int64_t tiles = ((int64_t(M) + BM - 1) / BM) * ((N + 127) / 128);
     const double pace = tn == 1 ? 1.07 : tn == 2 ? 1.0 : 1.03;
-    for (int sp = 1; sp <= max_splits && (sp == 1 || steps / sp >= 2); ++sp) {
+    const double part = max_splits > 1 ? double(M) * N * 8.0 / 1700.0 : 0.0;
+    for (int sp = 1; sp <= max_splits && (sp == 1 || steps / sp >= 2) && sp * part < best_t; ++sp) {
       const double mma = double((tiles * sp + ncu - 1) / ncu) * ((steps + sp - 1) / sp) * BM * kBKf32 * pace;
-      const double t = mma + (max_splits > 1 ? double(sp) * M * N * 8.0 / 1700.0 : 0.0);
+      const double t = mma + sp * part;
       if (t < best_t * (1.0 - 1e-9)) {
         best_t = t;
         best = GemmPlan{4, sp, tn};
@@ -542,7 +543,7 @@ static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int nc
 
 GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
   const int ncu = device_cu_count();
-  if (!bf16) return f32_plan(M, N, K, 16);
+  if (!bf16) return f32_plan(M, N, K, kMaxSplits);
   const int nk = K / kBK;
   // One workgroup per CU works best for these weight streams: a CU holding two
   // workgroups while others hold one doubles the kernel's critical path.  Pick the
@@ -579,7 +580,7 @@ static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int nc
       const double part = (double(M) * N + double(M2) * N2) * 8.0 / 3.8e6;
       int best_s = 1;
       double best_t = 1e30;
-      for (int s = 1; s <= 16 && tiles * s <= ncu && (s == 1 || nk / s >= 3); ++s) {
+      for (int s = 1; s <= kMaxSplits && tiles * s <= ncu && (s == 1 || nk / s >= 3); ++s) {
         const double t = step * ((nk + s - 1) / s) + part * s;
         if (t < best_t) {
           best_t = t;
@@ -595,7 +596,7 @@ static GemmPlan plan_stream(int BM, int M, int N, int M2, int N2, int nk, int nc
     const int bn = 32 * nw * tn;
     const int tiles = ((M + BM - 1) / BM) * ((N + bn - 1) / bn) +
                       ((M2 + BM - 1) / BM) * ((N2 + bn - 1) / bn);
-    for (int s = 1; s <= 16; ++s) {
+    for (int s = 1; s <= kMaxSplits; ++s) {
       if (s > 1 && nk / s < 8) break;
       const int wgs = tiles * s;
       const int rounds = (wgs + ncu - 1) / ncu;

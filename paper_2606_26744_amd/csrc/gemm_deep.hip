@@ -675,7 +675,7 @@ static GemmPlan deep_plan(int M, int N, int M2, int N2, int K, int max_splits, d
   GemmPlan best{4, 1, 2};
   best.bm = 256;
   double best_t = 1e30;
-  for (int sp = 1; sp <= max_splits && (sp == 1 || nk / sp >= 8); ++sp)
+  for (int sp = 1; sp <= max_splits && (sp == 1 || nk / sp >= 8) && part * sp < best_t; ++sp)
     for (const Shape& x : shapes) {
       const int bn = 128 * x.tn;
       const int64_t tiles = ((int64_t(M) + x.bm - 1) / x.bm) * ((N + bn - 1) / bn) +

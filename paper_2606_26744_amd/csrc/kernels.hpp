@@ -74,6 +74,7 @@ struct GemmArgs {
 };
 
 int gemm_k_align(bool bf16);                       // K must be a multiple of this
+constexpr int kMaxSplits = 16;                     // K splits of any plan, at most
 // Launch shape of a partial-sum GEMM: waves per workgroup (32 columns each; bf16:
 // 4, 6 or 8) and the number of K splits.
 struct GemmPlan {

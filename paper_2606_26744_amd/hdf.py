@@ -17,6 +17,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhdf.so")
 
 HDF_F32, HDF_BF16 = 0, 1
+HDF_E_WORKSPACE = 3
 STATUS = {0: "HDF_OK", 1: "HDF_E_INVALID", 2: "HDF_E_UNSUPPORTED", 3: "HDF_E_WORKSPACE",
           4: "HDF_E_HIP"}
 
@@ -533,6 +534,10 @@ class DrafterHandle:
     def workspace_bytes(self, n_seq: int, B: int, n_new: int, max_ctx: int) -> int:
         return int(lib().hdf_draft_block_workspace(ctypes.byref(self.s), n_seq, B, n_new, max_ctx))
 
+    def _workspace(self, n_seq, B, n_new, max_ctx, device) -> torch.Tensor:
+        return torch.empty(max(self.workspace_bytes(n_seq, B, n_new, max_ctx), 1), dtype=torch.uint8,
+                           device=device)
+
     def alloc_kv(self, kv_cap: int, device="cuda"):
         """KV cache tensors in the library's layout: keys and values each
         [L][nh][cap/64][64*hd], 64-position tiles in matrix-core operand order."""
@@ -562,9 +567,9 @@ class DrafterHandle:
         dev = tokens.device
         if hidden is None:
             hidden = torch.empty((n_seq * B, self.d), dtype=self.torch_dtype, device=dev)
-        need = self.workspace_bytes(n_seq, B, n_new, max_ctx)
-        if ws is None or ws.numel() < need:
-            ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+        if ws is None or ((not ws.is_cuda or not ws.is_contiguous()) and
+                          ws.numel() < self.workspace_bytes(n_seq, B, n_new, max_ctx)):
+            ws = self._workspace(n_seq, B, n_new, max_ctx, dev)
         if page_table is not None:
             if page_table.dtype != torch.int32 or page_table.dim() != 2 or \
                     page_table.shape[0] != n_seq or not page_table.is_contiguous():
@@ -574,19 +579,25 @@ class DrafterHandle:
                 raise ValueError("new_counts must be an int32 [n_seq] tensor")
             _dev(ctx_len, y_new, new_offsets, new_counts, page_table, kv_k, kv_vt, tokens, hidden,
                  ws)
-            _check(lib().hdf_draft_block_paged(
-                ctypes.byref(self.s), n_seq, B, _ptr(ctx_len), max_ctx, _ptr(y_new),
-                _ptr(new_offsets), _ptr(new_counts), n_new, _ptr(page_table), page_table.shape[1],
-                _ptr(kv_k),
-                _ptr(kv_vt), kv_k.shape[2], _ptr(tokens), _ptr(hidden), _ptr(ws), ws.numel(),
-                _stream(stream)))
-            return hidden
-        kv_cap = kv_k.shape[2] * 64
-        _dev(ctx_len, y_new, new_offsets, kv_offsets, kv_k, kv_vt, tokens, hidden, ws)
-        _check(lib().hdf_draft_block(ctypes.byref(self.s), n_seq, B, _ptr(ctx_len), max_ctx,
-                                     _ptr(y_new), _ptr(new_offsets), n_new, _ptr(kv_offsets),
-                                     _ptr(kv_k), _ptr(kv_vt), kv_cap, _ptr(tokens), _ptr(hidden),
-                                     _ptr(ws), ws.numel(), _stream(stream)))
+            def call(ws):
+                return lib().hdf_draft_block_paged(
+                    ctypes.byref(self.s), n_seq, B, _ptr(ctx_len), max_ctx, _ptr(y_new),
+                    _ptr(new_offsets), _ptr(new_counts), n_new, _ptr(page_table), page_table.shape[1],
+                    _ptr(kv_k), _ptr(kv_vt), kv_k.shape[2], _ptr(tokens), _ptr(hidden), _ptr(ws),
+                    ws.numel(), _stream(stream))
+        else:
+            _dev(ctx_len, y_new, new_offsets, kv_offsets, kv_k, kv_vt, tokens, hidden, ws)
+
+            def call(ws):
+                return lib().hdf_draft_block(
+                    ctypes.byref(self.s), n_seq, B, _ptr(ctx_len), max_ctx, _ptr(y_new),
+                    _ptr(new_offsets), n_new, _ptr(kv_offsets), _ptr(kv_k), _ptr(kv_vt),
+                    kv_k.shape[2] * 64, _ptr(tokens), _ptr(hidden), _ptr(ws), ws.numel(),
+                    _stream(stream))
+        st = call(ws)
+        if st == HDF_E_WORKSPACE:   # a given workspace of fewer bytes than this call's
+            st = call(self._workspace(n_seq, B, n_new, max_ctx, dev))
+        _check(st)
         return hidden
 
 
