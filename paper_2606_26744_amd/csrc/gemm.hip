@@ -559,10 +559,16 @@ GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K) {
 
 GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K) {
   // The row tiles of the first problem (at most two) read the same weight columns at
-  // about the same time on one XCD: 8-wave tiles with the weights fetched through L2.
-  // (4 waves for narrow problems, whose 8-wave tiles are few: 64 + 64 rows x 1024 -> 3072 48
-  // workgroups in place of 24, the two-layer step 150.9 -> 147.3 us.)
-  GemmPlan p = plan_stream(128, M, N, M2, N2, K / kBK, device_cu_count(), {4, 8});
+  // about the same time on one XCD: 8-wave tiles with the weights fetched through L2, or 4-wave
+  // ones where they fill the CUs as well or better, up to K = 4096.  Two-layer drafters (d_ff =
+  // 2d) of 4 x 16 block rows, 4 and 8 waves offered against 8: d = 2304 153 us against 156,
+  // 2560 163.5 / 166.5, 3072 188 / 192, 3584 217 / 218.5; beyond, where half the weight bytes
+  // in flight cost more than the fill gives, 5120 335 / 328 and with 8 x 16 rows 425 / 419, 6144
+  // 526.5 / 521.  (Short K takes 4 waves: 64 + 64 rows x 1024 -> 3072 48 workgroups in place of
+  // 24, the two-layer step 150.9 -> 147.3 us.)
+  const int nk = K / kBK, ncu = device_cu_count();
+  GemmPlan p = K <= 4096 ? plan_stream(128, M, N, M2, N2, nk, ncu, {4, 8})
+                         : plan_stream(128, M, N, M2, N2, nk, ncu, {8});
   p.nt = false;
   return p;
 }

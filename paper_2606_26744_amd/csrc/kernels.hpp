@@ -88,7 +88,8 @@ GemmPlan gemm_plan(bool bf16, int M, int N, int K);
 // Plan of two problems of the same K launched together (M2 = 0: one problem).
 GemmPlan gemm_plan2(bool bf16, int M, int N, int M2, int N2, int K);
 // Two problems of the same K in one launch where the first one's row tiles (up to 256
-// rows) share weight columns: weights fetched through L2 (8 waves of one block).
+// rows) share weight columns: weights fetched through L2 (4 or 8 waves of one
+// block, 8 for K above 4096).
 GemmPlan gemm_plan_shared(int M, int N, int M2, int N2, int K);
 // Matrix-core bound bf16 problems (gemm_deep.hip): the plan, and the launch with epilogue
 // `epi` (kEpiPartial by the plan's splits, the others in one).
