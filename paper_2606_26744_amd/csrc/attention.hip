@@ -46,6 +46,7 @@ namespace hdf {
 constexpr int kCombineThreads = 256;
 constexpr int kKeyTile = 64;
 constexpr int kMaxChunkTiles = kAttnMaxChunk / kKeyTile;
+constexpr size_t kMaxLdsBytes = 160 * 1024;   // of a workgroup
 constexpr int kAttnSortSeqs = 1024;   // longest-context-first dispatch up to this many sequences
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -431,7 +432,9 @@ attn_kernel(AttnArgs a, T* __restrict__ out) {
 // Merge the chunk partials of one (sequence, head, 16-query group) -> O rows.
 // Phase 1 reads every chunk's (m, l), phase 2 turns them into per-chunk weights
 // exp2(m_c - M) / L, phase 3 forms each output quad from independent loads.
-template <typename T>
+// The weights stay in LDS, or where that cannot hold them (IN_LDS false: more than about 1280
+// chunks, one or two heads over 660 thousand positions and more) in the place of the (m, l).
+template <typename T, bool IN_LDS>
 __global__ void __launch_bounds__(kCombineThreads)
 attn_combine_kernel(AttnArgs a, T* __restrict__ out) {
   extern __shared__ float cw[];  // [16][n_chunks + 1] weights, then [16][n_chunks + 1] m
@@ -444,30 +447,38 @@ attn_combine_kernel(AttnArgs a, T* __restrict__ out) {
   float* cm = cw + 16 * NC;
   const int d = a.nh * a.hd;
   const int64_t base = (int64_t(s) * a.nh + h) * NC;
-  // Phase 1: (m, l) of every chunk of the sequence (the block's is chunk n_chunks).
-  for (int e = threadIdx.x; e < 16 * nc; e += kCombineThreads) {
-    const int qq = e / nc;
-    const int c = e - qq * nc;
+  // (m, l) of query qq in chunk c of the sequence (the block's is chunk n_chunks).
+  auto ml = [&](int qq, int c) {
     const int cc = (c == nc - 1) ? a.n_chunks : c;
-    const int64_t pi = (base + cc) * a.QB + qg * 16 + qq;
-    cm[qq * NC + c] = a.part_ml[pi * 2];
-    cw[qq * NC + c] = a.part_ml[pi * 2 + 1];
+    return a.part_ml + ((base + cc) * a.QB + qg * 16 + qq) * 2;
+  };
+  auto m_of = [&](int qq, int c) -> float& { return IN_LDS ? cm[qq * NC + c] : ml(qq, c)[0]; };
+  auto w_of = [&](int qq, int c) -> float& { return IN_LDS ? cw[qq * NC + c] : ml(qq, c)[1]; };
+  // Phase 1.
+  if constexpr (IN_LDS) {
+    for (int e = threadIdx.x; e < 16 * nc; e += kCombineThreads) {
+      const int qq = e / nc;
+      const int c = e - qq * nc;
+      cm[qq * NC + c] = ml(qq, c)[0];
+      cw[qq * NC + c] = ml(qq, c)[1];
+    }
+    __syncthreads();
   }
-  __syncthreads();
   // Phase 2: per-query weights.
   if (threadIdx.x < 16) {
     const int qq = threadIdx.x;
     float mm = -INFINITY;
-    for (int c = 0; c < nc; ++c) mm = fmaxf(mm, cm[qq * NC + c]);
+    for (int c = 0; c < nc; ++c) mm = fmaxf(mm, m_of(qq, c));
     float l = 0.f;
     for (int c = 0; c < nc; ++c) {
-      const float f = (cm[qq * NC + c] == -INFINITY) ? 0.f : soft_exp<T>(cm[qq * NC + c] - mm);
-      cm[qq * NC + c] = f;
-      l += f * cw[qq * NC + c];
+      const float f = (m_of(qq, c) == -INFINITY) ? 0.f : soft_exp<T>(m_of(qq, c) - mm);
+      m_of(qq, c) = f;
+      l += f * w_of(qq, c);
     }
     const float inv = 1.f / l;
-    for (int c = 0; c < nc; ++c) cw[qq * NC + c] = cm[qq * NC + c] * inv;
+    for (int c = 0; c < nc; ++c) w_of(qq, c) = m_of(qq, c) * inv;
   }
+  __threadfence_block();
   __syncthreads();
   // Phase 3: outputs, four consecutive dims per item.
   const int quads = a.hd / 4;
@@ -478,7 +489,7 @@ attn_combine_kernel(AttnArgs a, T* __restrict__ out) {
     const int i0 = (e - qq * quads) * 4;
     float o[4] = {0.f, 0.f, 0.f, 0.f};
     for (int c = 0; c < nc; ++c) {
-      const float wgt = cw[qq * NC + c];
+      const float wgt = w_of(qq, c);
       const int cc = (c == nc - 1) ? a.n_chunks : c;
       const float4 v = *reinterpret_cast<const float4*>(
           a.part_o + ((base + cc) * a.QB + q) * a.hd + i0);
@@ -506,8 +517,11 @@ static hipError_t launch_attn(const AttnArgs& a, const dim3& grid, T* out, hipSt
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_chunks == 1) return e;
   const size_t lds = size_t(2) * 16 * (a.n_chunks + 1) * sizeof(float);
-  hipLaunchKernelGGL(attn_combine_kernel<T>, dim3(a.n_seq * ((a.B + 15) / 16), a.nh),
-                     dim3(kCombineThreads), lds, s, a, out);
+  const dim3 rows(a.n_seq * ((a.B + 15) / 16), a.nh);
+  if (lds <= kMaxLdsBytes)
+    hipLaunchKernelGGL((attn_combine_kernel<T, true>), rows, dim3(kCombineThreads), lds, s, a, out);
+  else
+    hipLaunchKernelGGL((attn_combine_kernel<T, false>), rows, dim3(kCombineThreads), 0, s, a, out);
   return hipGetLastError();
 }
 

@@ -337,3 +337,14 @@ def test_gated_product_above_128_rows(n_seq, B, d, F):
     wl.drafter = synth.DrafterShape(d=d, n_layers=1, n_heads=d // 64, head_dim=64, d_ff=F, vocab=600)
     ctx = [40 + 7 * s for s in range(n_seq)]
     _compare(DraftCase(wl, ctx, [3] * n_seq, B=B, sub=51), seqs=[0, n_seq // 2, n_seq - 1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_more_chunks_than_the_merge_holds_in_lds(dtype):
+    """One head over 670 thousand positions: 1309 chunks, whose merge weights exceed a
+    workgroup's 160 KB of LDS."""
+    wl = synth.tiny_fp32() if dtype == "f32" else synth.small_bf16()
+    wl.d = 128
+    wl.drafter = synth.DrafterShape(d=128, n_layers=1, n_heads=1, head_dim=128, d_ff=256, vocab=500)
+    _compare(DraftCase(wl, [670_000], [40], sub=61, rope=False))
+    torch.cuda.empty_cache()
