@@ -9,6 +9,7 @@ from oracle.drafter import context_kv, draft_block as ref_draft
 from oracle.numerics import as_f64
 from paper_2606_26744_amd import hdf
 from tests._case import DraftCase, bits
+from tests._plans import deep_tile, gemm_gated_plan
 from tests._tol import assert_bf16_state_close, assert_f32_rows_close
 
 pytestmark = pytest.mark.gpu
@@ -330,13 +331,28 @@ def test_cold_rows_stored_by_the_projection(hd, ctx, new, rope):
 
 @pytest.mark.parametrize("n_seq,B,d,F", [(9, 16, 512, 1024), (13, 20, 512, 704), (40, 16, 1024, 192)])
 def test_gated_product_above_128_rows(n_seq, B, d, F):
-    """More than 128 block rows: the activation of the gate and up product in its epilogue, with
-    ragged last row and column tiles (F an odd multiple of 64 among them)."""
+    """More than 128 block rows: the activation of the gate and up product in the epilogue of 128 x
+    256 tiles, with ragged last row and column tiles (F an odd multiple of 64 among them); the
+    last shape goes through partial sums."""
     wl = synth.small_bf16()
     wl.d = d
     wl.drafter = synth.DrafterShape(d=d, n_layers=1, n_heads=d // 64, head_dim=64, d_ff=F, vocab=600)
     ctx = [40 + 7 * s for s in range(n_seq)]
     _compare(DraftCase(wl, ctx, [3] * n_seq, B=B, sub=51), seqs=[0, n_seq // 2, n_seq - 1])
+
+
+@pytest.mark.parametrize("n_seq,B,d,F,tile", [(60, 15, 384, 4160, (256, 256)), (54, 15, 384, 8256, (128, 512)),
+                                              (9, 16, 512, 1024, (128, 256))])
+def test_gated_product_tiles(n_seq, B, d, F, tile):
+    """The gated product in each of its tiles: rows that end inside a tile and, in the large
+    ones, a last column tile whose blocks past F (an odd multiple of 64) are clamped."""
+    assert deep_tile(gemm_gated_plan(n_seq * B, F, d)) == tile
+    assert (n_seq * B) % tile[0] != 0 and (tile == (128, 256) or (2 * F) % tile[1] != 0)
+    wl = synth.small_bf16()
+    wl.d = d
+    wl.drafter = synth.DrafterShape(d=d, n_layers=1, n_heads=d // 64, head_dim=64, d_ff=F, vocab=600)
+    ctx = [40 + 7 * s for s in range(n_seq)]
+    _compare(DraftCase(wl, ctx, [3] * n_seq, B=B, sub=52), seqs=[0, n_seq // 2, n_seq - 1])
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -9,6 +9,7 @@ import synth
 from oracle.fc_reducer import fc_reduce as ref_fc
 from oracle.numerics import as_f64
 from paper_2606_26744_amd import hdf
+from tests._plans import deep_tile, gemm_plan
 from tests._tol import assert_bf16_close, assert_f32_rows_close
 
 pytestmark = pytest.mark.gpu
@@ -99,8 +100,8 @@ def test_fp32_k_steps(n, m, d):
 @pytest.mark.parametrize("n,m,d", [(129, 3, 64), (256, 5, 64), (255, 1, 576), (513, 7, 192), (1025, 2, 1088),
                                    (2049, 3, 320), (2177, 5, 64), (4100, 1, 704)])
 def test_matrix_core_tiles(n, m, d):
-    """The matrix-core bound tiles around their row and column edges, both tile shapes, and K
-    of one, three, five, seven and more 64-K steps (a part of the loop's unrolled units)."""
+    """The 128 x 256 matrix-core bound tiles around their row and column edges, and K of one,
+    three, five, seven and more 64-K steps (a part of the loop's unrolled units)."""
     _case(n, m, d, "bf16", n + m, n % 2 == 0)
 
 
@@ -108,3 +109,15 @@ def test_matrix_core_tiles(n, m, d):
 def test_matrix_core_small_tiles(n, m, d):
     """Shapes whose plan takes the 128 x 256 tiles, with and without K splits."""
     _case(n, m, d, "bf16", n + m, n % 2 == 0)
+
+
+@pytest.mark.parametrize("n,m,d,tile,splits", [(2026, 1, 4160, (256, 256), 1), (4622, 1, 1600, (128, 512), 1),
+                                               (1538, 1, 2368, (256, 256), 3), (3264, 2, 1088, (128, 512), 3)])
+def test_matrix_core_large_tiles(n, m, d, tile, splits):
+    """The two large tiles with a ragged last row and column tile, bias, and a K range that is no
+    multiple of the loop's unrolled units: bf16 rows from the epilogue and partial sums of K
+    splits."""
+    p = gemm_plan(True, n, d, m * d)
+    assert (deep_tile(p), p.splits) == (tile, splits)
+    assert n % tile[0] != 0 and d % tile[1] != 0
+    _case(n, m, d, "bf16", n + m, True)
