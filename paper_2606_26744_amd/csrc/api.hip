@@ -328,7 +328,7 @@ hdf_status hdf_fc_reduce(const void* H, const void* W_fc, const float* b_fc, int
     if (bf && pl.tn > 1 && pl.splits == 1) {
       // One K split on the matrix-core bound tiles: bias, rounding and the rows' stores happen
       // in the product's epilogue (the fp32 rows and the pass over them took 83 us of 1679 at
-      // 16384 rows of 4096, besides their stores).
+      // 16384 rows of 4096, besides their stores).  d % 8 == 0 there: m * d % 64 == 0 with m <= 8.
       const hipError_t e = hdf::launch_gemm_rows(static_cast<const char*>(H) + r0 * K * el, K, W_fc, rows,
                                                  d, K, pl, b_fc, static_cast<char*>(Y) + r0 * d * el, s);
       if (e != hipSuccess) return hip_fail(e, "fc_reduce gemm");

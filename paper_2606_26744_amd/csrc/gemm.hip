@@ -41,10 +41,9 @@ constexpr int kBK = 64;        // K granularity of the bf16 tiles (K % kBK == 0)
 constexpr int kShortSteps = 32;   // K steps up to which the stream plan weighs steps against partials
 constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last half step is zero-filled)
 
-// TN: 32-column weight blocks per wave (1, 2 or 4).  Each activation fragment read from
-// LDS feeds TN matrix-core operations, so wider waves cut the LDS traffic per MFMA; the
-// compute-bound shapes (a few hundred rows and more) need it, the weight streams of
-// 128 rows prefer more waves per CU instead.
+// TN: 32-column weight blocks per wave, 1, or 2 in the LM head's stream.  Each activation
+// fragment read from LDS feeds TN matrix-core operations, so wider waves cut the LDS traffic
+// per MFMA; the split weight streams prefer more waves per CU instead.
 // NT: fetch the weights with non-temporal loads (they stream past the caches).  Right
 // when one row tile reads every weight byte once; with several row tiles the others
 // re-read the weights from L2, so they are fetched through the caches.
@@ -52,7 +51,7 @@ constexpr int kBKf32 = 32;     // K step of the fp32 tiles (K % 16 == 0; a last 
 // bytes of every activation row in either type, so the fp32 step is 32 of K; a packed
 // 32 x 16 block is 32 bytes a lane (two loads), and lane l's eight values (row l%32, k
 // 8*(l/32)..+7) are the operands of eight MFMAs, each taking k pair (e, 8 + e).
-template <typename T, int BM, int NW, int STAGES, int EPI, int TN = 1, bool NT = (TN == 1)>
+template <typename T, int BM, int NW, int STAGES, int EPI, int TN, bool NT>
 __global__ void __launch_bounds__(NW * 64)
 gemm_kernel(GemmArgs p) {
   constexpr bool F32 = sizeof(T) == 4;
@@ -389,8 +388,9 @@ __global__ void pack_weight_kernel(const T* __restrict__ src, T* __restrict__ ds
 
 // ---------------------------------------------------------------------------- host side
 
-template <int NW, int TN, int STAGES = 4, bool NT = (TN == 1)>
+template <int NW, int STAGES, bool NT>
 static void launch_bf16_partial(const GemmArgs& a, int splits, hipStream_t s) {
+  constexpr int TN = 1;
   const int BM = (a.M <= 64 && a.M2 <= 64) ? 64 : 128;
   constexpr int BN = 32 * NW * TN;
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) +
@@ -405,10 +405,11 @@ static void launch_bf16_partial(const GemmArgs& a, int splits, hipStream_t s) {
 }
 
 // One pass for 128 < M <= 192 rows: every row in one tile, 8 waves of one 32-column block,
-// the weights streamed once (non-temporal): 221 us for 129280 columns of 4096, against 227 to
-// 239 on the matrix-core bound tiles, which pad the rows to 256 and re-read the weights
-// through L2.  Above 192 rows those tiles are the faster ones (208 rows 239 against 266 us for
-// one tile of 256 rows, whose activation fragments are the LDS bandwidth of the CU).
+// the weights streamed once (non-temporal).  In turns with the matrix-core bound tiles, which pad
+// the rows to 256, 129280 columns of 4096: 192 rows 217 us here, 193 rows 227 there (32000
+// columns, 125 workgroups of either: 76 and 78).  Above 192 rows those are the faster ones (208
+// rows 234-239 against 266 us for one tile of 256 rows, whose activation fragments are the LDS
+// bandwidth of the CU).
 static void launch_bf16_argmax_tall(const GemmArgs& a, hipStream_t s) {
   constexpr int BN = 32 * 8;
   const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(8 * 64);
@@ -417,16 +418,11 @@ static void launch_bf16_argmax_tall(const GemmArgs& a, hipStream_t s) {
 
 // Up to 128 rows: one row tile, every weight byte is read once, so the weights stream past the
 // caches.
-template <int NW, int TN, int STAGES>
+template <int BM, int NW, int TN, int STAGES>
 static void launch_bf16_argmax_stream(const GemmArgs& a, hipStream_t s) {
   constexpr int BN = 32 * NW * TN;
-  const dim3 grid((a.N + BN - 1) / BN, 1, 1), block(NW * 64);
-  if (a.M <= 64)
-    hipLaunchKernelGGL((gemm_kernel<bf16_t, 64, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
-                       s, a);
-  else
-    hipLaunchKernelGGL((gemm_kernel<bf16_t, 128, NW, STAGES, kEpiArgmax, TN, true>), grid, block, 0,
-                       s, a);
+  hipLaunchKernelGGL((gemm_kernel<bf16_t, BM, NW, STAGES, kEpiArgmax, TN, true>),
+                     dim3((a.N + BN - 1) / BN), dim3(NW * 64), 0, s, a);
 }
 
 // The narrowest tile that covers the vocabulary in one round of workgroups: 128, 256 or 512
@@ -436,16 +432,13 @@ static void launch_bf16_argmax_stream(const GemmArgs& a, hipStream_t s) {
 // columns 121, 129, 142).  Ring depths as measured at each width.
 static void launch_bf16_argmax(const GemmArgs& a, hipStream_t s) {
   const int ncu = device_cu_count();
-  if ((int64_t(a.N) + 127) / 128 <= ncu) {
-    if (a.M <= 64)
-      launch_bf16_argmax_stream<4, 1, 4>(a, s);
-    else
-      launch_bf16_argmax_stream<4, 1, 2>(a, s);
-  } else if ((int64_t(a.N) + 255) / 256 <= ncu) {
-    launch_bf16_argmax_stream<8, 1, 2>(a, s);
-  } else {
-    launch_bf16_argmax_stream<8, 2, 2>(a, s);
-  }
+  const bool low = a.M <= 64;
+  if ((int64_t(a.N) + 127) / 128 <= ncu)
+    low ? launch_bf16_argmax_stream<64, 4, 1, 4>(a, s) : launch_bf16_argmax_stream<128, 4, 1, 2>(a, s);
+  else if ((int64_t(a.N) + 255) / 256 <= ncu)
+    low ? launch_bf16_argmax_stream<64, 8, 1, 2>(a, s) : launch_bf16_argmax_stream<128, 8, 1, 2>(a, s);
+  else
+    low ? launch_bf16_argmax_stream<64, 8, 2, 2>(a, s) : launch_bf16_argmax_stream<128, 8, 2, 2>(a, s);
 }
 
 // fp32 tiles: 4 waves of one 32-column block and 32, 64 or 128 rows (the plan's tn row
@@ -508,15 +501,15 @@ static hipError_t launch_gemm_any(bool bf16, int epi, const GemmArgs& a, GemmPla
     if (epi == kEpiPartial) {
       if (plan.tn > 1) return launch_gemm_deep(kEpiPartial, a, plan, s);
       if (!plan.nt && plan.nw == 4) {
-        launch_bf16_partial<4, 1, 4, false>(a, plan.splits, s);
+        launch_bf16_partial<4, 4, false>(a, plan.splits, s);
       } else if (!plan.nt) {
-        launch_bf16_partial<8, 1, 4, false>(a, plan.splits, s);
+        launch_bf16_partial<8, 4, false>(a, plan.splits, s);
       } else if (plan.nw == 8) {
-        launch_bf16_partial<8, 1>(a, plan.splits, s);
+        launch_bf16_partial<8, 4, true>(a, plan.splits, s);
       } else if (plan.nw == 6) {
-        launch_bf16_partial<6, 1, 3>(a, plan.splits, s);
+        launch_bf16_partial<6, 3, true>(a, plan.splits, s);
       } else {
-        launch_bf16_partial<4, 1, 2>(a, plan.splits, s);
+        launch_bf16_partial<4, 2, true>(a, plan.splits, s);
       }
     } else {
       if (a.M > 192) return launch_gemm_deep(kEpiArgmax, a, deep_argmax_plan(a.M), s);
@@ -656,7 +649,7 @@ hipError_t launch_gemm_partial2(const void* A, int64_t lda, const void* B, int M
 
 hipError_t launch_gemm_rows(const void* A, int64_t lda, const void* B, int M, int N, int K,
                             GemmPlan plan, const float* bias, void* out, hipStream_t s) {
-  if (plan.tn < 2 || plan.splits != 1 || N % 4 != 0) return hipErrorInvalidValue;
+  if (plan.tn < 2 || plan.splits != 1 || N % 8 != 0) return hipErrorInvalidValue;
   GemmArgs a{};
   a.A = A; a.lda = lda; a.B = B;
   a.M = M; a.N = N; a.K = K; a.out = out; a.bias = bias;

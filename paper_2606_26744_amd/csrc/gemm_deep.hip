@@ -440,7 +440,6 @@ __device__ __forceinline__ void store_rows(const f32x16_t (&acc)[TM][TN], const 
   lds_barrier();
   bias += (threadIdx.x >> 6) * W + 4 * h;
   bf16_t* out = static_cast<bf16_t*>(p.out);
-  const bool whole = (p.N & 7) == 0;            // rows start on 16 bytes (else on 8)
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
@@ -460,15 +459,7 @@ __device__ __forceinline__ void store_rows(const f32x16_t (&acc)[TM][TN], const 
       const int r = q * RPI + lane / PER, c = (lane % PER) * 8;
       const u32x4 v = *reinterpret_cast<const u32x4*>(own + r * LD + c);
       const int row = m0 + 32 * i + r, col = c0 + c;
-      if (row < p.M && col < p.N) {
-        bf16_t* dst = out + int64_t(row) * p.N + col;
-        if (whole) {
-          st16(dst, v);
-        } else {
-          *reinterpret_cast<uint2*>(dst) = make_uint2(v[0], v[1]);
-          if (col + 4 < p.N) *reinterpret_cast<uint2*>(dst + 4) = make_uint2(v[2], v[3]);
-        }
-      }
+      if (row < p.M && col < p.N) st16(out + int64_t(row) * p.N + col, v);   // N is a multiple of 8
     }
     __builtin_amdgcn_wave_barrier();
   }

@@ -67,7 +67,7 @@ struct GemmArgs {
   void* vtc;              // [nh][hd][cap] value tiles of the layer
   int64_t cap;
   int kv_d, hd;
-  // kEpiRows: out[M][N] bf16 (16-byte aligned), N % 4 == 0; bias [N] fp32 or NULL.
+  // kEpiRows: out[M][N] bf16 (16-byte aligned), N % 8 == 0; bias [N] fp32 or NULL.
   // kEpiGated: W the stacked [gate; up], out[M][N/2] bf16, N/2 a multiple of 64.
   void* out;
   const float* bias;
