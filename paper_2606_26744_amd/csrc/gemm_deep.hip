@@ -24,9 +24,10 @@
 // Measured alone (random operands, warm): 16384 x 4096 -> 8192 972 -> 815 us with fp32 stores,
 // 16384 x 16384 -> 4096 1878 -> 1520 us, 1024 x 4096 -> 24576 in two K splits 204 -> 180 us,
 // 1024 x 12288 -> 4096 in four 96 -> 81 us (before: compiler-ordered loop of the 128 x 512
-// tiles).  With the other epilogues, same box: keys and values 838 us, bf16 rows 830, argmax
-// 779, fp32 rows 837.  Copies without stores run at 1.40-1.52 PFLOP/s, without any load from memory in
-// the loop at 1.60-1.72, the MFMAs alone at 1.67-1.80 (the power limit on such data).
+// tiles).  With the other epilogues, same box: keys and values 838 us (846 at the least and 870
+// on average inside the cold step), bf16 rows 830, argmax 779, fp32 rows 837.  Copies without
+// stores run at 1.40-1.52 PFLOP/s, without any load from memory in the loop at 1.60-1.72, the
+// MFMAs alone at 1.67-1.80 (the power limit on such data).
 #include "common.hpp"
 #include "deep_schedule.hpp"
 #include "gemm_tile.hpp"

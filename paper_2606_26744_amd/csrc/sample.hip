@@ -148,8 +148,8 @@ __device__ RowState block_merge(RowState st, RowState* sh) {
 // The drawing pass is bound by the vector unit's integer products (a Philox block of eight
 // uniforms is about 62 32-bit products after the shared halves are taken out), not by its
 // 16-byte loads: 128 rows x 129280, 43.6 -> 31.7 us with 32-bit halves in the generator and
-// the race in place of two logarithms an entry.  The pass without draws streams the rows
-// (14.7 us, 4.5 TB/s).
+// the race in place of two logarithms an entry, 32.8 with the uniforms' rounding taken off.  The
+// pass without draws streams the rows (14.7 us, 4.5 TB/s).
 // Pass over logits row `row`, columns [c0, c1) (c0 % 8 == 0): partial log-sum-exp of
 // logits * inv_t and, with SAMPLE, the Gumbel-max draw.  Partial j of the row goes to
 // part[row * n_parts + j].  Each thread loads kGroupsPerPass groups of eight logits
